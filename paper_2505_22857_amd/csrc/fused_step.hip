@@ -1,7 +1,7 @@
-// Greedy shallow fusion (Section 2.3): one step over a batch of hypotheses, and
-// a whole decode over all frames of a batch of utterances in one launch.
+// Greedy shallow fusion (Section 2.3), one step over a batch of hypotheses, and
+// the top-k beam expansion.
 //
-// One workgroup of W wavefronts per hypothesis (W = 4 for batches up to 512,
+// One workgroup of W wavefronts per hypothesis (W = 4 for batches up to 1024,
 // else 1), each wavefront owning every W-th stripe of 256 tokens.  CTC and
 // transducer modes first take the plain ASR argmax over the V + 1 classes;
 // when that keeps blank (or, for CTC, the previous label) the LM is not
@@ -16,21 +16,13 @@
 // (value, ~index) in one LDS exchange.  The winner's next state rides along with its key.  No
 // MFMA: one fma and one compare per token.
 //
-// The decode kernel keeps each utterance's state and previous label in
-// registers across frames: frame t + 1 depends on frame t only through them,
-// so a single launch replaces T launches and their host round trips.
-//
 // AED mode (Section 2.3): class V is <eos>, whose LM score is the state's
 // final weight (the </s> score, precomputed per state); <eos> keeps the state.
 #include <hip/hip_runtime.h>
 
-#include <atomic>
-
-#include "walk.h"
+#include "group.h"
 
 namespace ngpu {
-
-enum { kPlain = 0, kCtc = 1, kTransducer = 2, kAed = 3 };
 
 // Words of an ASR row buffer in LDS: the V tokens rounded up to whole
 // stripes, so that the 16-byte reads of the scans stay inside it.  (Blank or
@@ -97,143 +89,6 @@ struct LdsAsr {
     }
 };
 
-// ASR row held in registers, for V <= kRegTokens: lane l of wavefront w keeps
-// classes 256 c + 64 j + l (j = 0 .. 3) of each owned stripe c, in ascending
-// order, so each of its loads is one coalesced 256-byte read and the scans
-// read the walked LDS row one word per lane (no bank conflicts).  The row is
-// read through a buffer resource of V words: classes past V read as 0 without
-// a branch (the scans skip them), so the loads are straight-line code and the
-// compiler's waits for the chain record issued just before them can leave
-// them in flight.  FULL: V = kRegTokens, every class present and nothing to
-// skip (the per-class conditions would otherwise be held across the frame
-// loop in scalar registers).
-constexpr int kRegTokens = 1024;
-
-template <int W, bool FULL>
-struct RegAsr {
-    static constexpr int kN = kRegTokens / (kWave * W);   // values per lane
-    float a[kN];
-
-    // first class of value i of this wavefront (uniform); the lane adds its index
-    __device__ static __forceinline__ int base(int i, int wave) {
-        return kStripe * (W * (i / 4) + (W == 1 ? 0 : wave)) + kWave * (i % 4);
-    }
-
-    // (the resource starts at this wavefront's first stripe: the range check
-    // covers the lane and instruction offsets, not a scalar offset)
-    __device__ __forceinline__ void load(const float *row, int V, int wave, int lane) {
-        const int w0 = W == 1 ? 0 : kStripe * wave;
-        const int n = V > w0 ? V - w0 : 0;
-        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(row + w0), short(0),
-                                                                           n * int(sizeof(float)), kBufferConfig);
-#pragma unroll
-        for (int i = 0; i < kN; ++i)
-            a[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
-                                                 r, (kStripe * W * (i / 4) + kWave * (i % 4) + lane) * int(sizeof(float)),
-                                                 0, 0));
-    }
-    __device__ __forceinline__ void argmax(int V, int wave, int lane, float &bx, int &bi) const {
-#pragma unroll
-        for (int i = 0; i < kN; ++i) {
-            const int v = base(i, wave) + lane;
-            if (FULL || base(i, wave) + kWave <= V || v < V) take_max(a[i], v, bx, bi);
-        }
-    }
-    __device__ __forceinline__ void fused(const ChainHead &h, const float *ls, const int *ln, float lambda, int V,
-                                          int wave, int lane, float &bx, int &bi) const {
-#pragma unroll
-        for (int i = 0; i < kN; ++i) {
-            const int b0 = base(i, wave);
-            if (!FULL && b0 >= V) continue;   // uniform; the slots read below lie inside the padded row
-            const int v = b0 + lane;
-            float lm;
-            int nx;
-            slot_value(h, ls[v], ln[v], lm, nx);
-            const float f = __builtin_fmaf(lambda, lm, a[i]);
-            if (FULL || b0 + kWave <= V || v < V) take_max(f, v, bx, bi);
-        }
-    }
-};
-
-// One wavefront's copy of a compact dense row (DevTrie::dense_c), for the
-// whole decode with rows in registers (W = 1): lane l keeps tokens 64 i + l,
-// loaded like the ASR row (tokens past V read as 0 and are never used).
-template <bool FULL>
-struct CompactRow {
-    float c[kRegTokens / kWave];
-
-    __device__ __forceinline__ void load(const float *row, int V, int lane) {
-        const __amdgpu_buffer_rsrc_t r =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(row), short(0), V * int(sizeof(float)), kBufferConfig);
-#pragma unroll
-        for (int i = 0; i < kRegTokens / kWave; ++i)
-            c[i] = __builtin_bit_cast(float,
-                                      __builtin_amdgcn_raw_buffer_load_b32(r, (kWave * i + lane) * int(sizeof(float)), 0, 0));
-    }
-
-    // Per-lane argmax of fmaf(lambda, lm[v], asr[v]): lm[v] from the LDS row
-    // where a sparse level wrote it (kFinal in ln), else from this row: its
-    // weight (the stored magnitude with the sign bit set) plus acc0 where the
-    // sign bit marks a backed-off entry, acc1 otherwise.
-    __device__ __forceinline__ void fused(const ChainHead &h, const float *ls, const int *ln,
-                                          const RegAsr<1, FULL> &asr, float lambda, int V, int lane, float &bx,
-                                          int &bi) const {
-#pragma unroll
-        for (int i = 0; i < kRegTokens / kWave; ++i) {
-            const int b0 = kWave * i;
-            if (!FULL && b0 >= V) continue;   // uniform; the slots read below lie inside the padded row
-            const int v = b0 + lane;
-            // (both words read unconditionally: a read inside the select
-            // becomes a branch with its own wait, per token)
-            const int n = ln[v];
-            const float x = ls[v];
-            const unsigned cb = __float_as_uint(c[i]);
-            const float dense = ((cb >> 31) ? h.acc0 : h.acc1) + __uint_as_float(cb | 0x80000000u);
-            const float lm = (n & kFinal) ? x : dense;
-            const float f = __builtin_fmaf(lambda, lm, asr.a[i]);
-            if (FULL || b0 + kWave <= V || v < V) take_max(f, v, bx, bi);
-        }
-    }
-
-    // Next state of token w (uniform, w < V): the sparse level's where one
-    // wrote the slot; else, for an own entry of the row when the image
-    // numbers them by rank (orders >= 3), the row's first own-bigram state
-    // (base) plus the number of own entries below w (one ballot per 64
-    // tokens); else the unigram state first[1] + w.
-    __device__ __forceinline__ int next_state(const DevTrie &t, const int *ln, int base, int w, int V,
-                                              int lane) const {
-        const int n = ln[w];
-        if (n & kFinal) return n & kStateMask;
-        const int j = w >> 6, b = w & (kWave - 1);
-        int rank = 0;
-        bool own = false;
-#pragma unroll
-        for (int i = 0; i < kRegTokens / kWave; ++i) {
-            if (i > j) continue;   // uniform
-            const bool mine = (FULL || kWave * i + lane < V) && !(__float_as_uint(c[i]) >> 31);
-            const unsigned long long m = __ballot(mine);
-            if (i < j) {
-                rank += __builtin_popcountll(m);
-            } else {
-                rank += __builtin_popcountll(m & ((1ull << b) - 1ull));
-                own = (m >> b) & 1ull;
-            }
-        }
-        return own && t.compact_rank ? base + rank : t.first[1] + w;
-    }
-};
-
-// Clears the kFinal marks of the LDS next-state row (lds_row(V) words) before
-// the sparse levels write theirs: with compact rows no dense copy overwrites it.
-__device__ __forceinline__ void clear_marks(int *ln, int V, int lane) {
-    const i32x4 z = {0, 0, 0, 0};
-    for (int c = 4 * lane; c < lds_row(V); c += 4 * kWave) *reinterpret_cast<i32x4 *>(ln + c) = z;
-}
-
-struct NoHook {
-    __device__ __forceinline__ void operator()() const {}
-};
-
 // Exchange area of W wavefronts: two alternating buffers of W (key, payload)
 // pairs, so one barrier per exchange suffices (a buffer is written again only
 // after every wavefront has passed the next exchange's barrier).
@@ -241,11 +96,6 @@ struct Exchange {
     unsigned long long key[2][4];
     int payload[2][4];
 };
-
-// Waits until this wavefront's LDS writes are done, then for all wavefronts
-// of the workgroup.  The memory clobber keeps the compiler from moving any
-// memory access across it.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // Argmax over the W wavefronts' lanes of (bx, bi): lowest index among the
 // largest values.  Returns the index (kNone when every value was -inf), its
@@ -307,43 +157,34 @@ __device__ __forceinline__ int first_token_state(const ChainHead &h, const float
 }
 
 // One fused greedy step of a hypothesis held by W wavefronts.  asr: its V
-// token ASR log-probabilities (LdsAsr: owned stripes landed unless
-// ROW_PENDING, in which case their copy was issued just before; RegAsr);
+// token ASR log-probabilities, whose copy into LDS was issued just before;
 // rowV: class V (blank, or <eos> in AED mode).  s: valid state (uniform); pv:
-// previous label (CTC).  after_record runs once the chain record's load is
-// issued.  Returns the label and updates s; all lanes of all W wavefronts
-// return the same values.
-template <int MODE, int W, bool ROW_PENDING, class Asr, class AfterRecord = NoHook, bool SPLIT = false,
-          class Index = KernargTables>
-__device__ __forceinline__ int greedy_step(const DevTrie &t, const Index &ci, const Asr &asr, float rowV,
-                                           float lambda, int &s,
-                                           int pv, float *ls, int *ln, Exchange *xc, int &xi, int wave, int lane,
-                                           const float *pf_src = nullptr, float *pf_dst = nullptr, int pf_n = 0,
-                                           AfterRecord after_record = {}) {
+// previous label (CTC).  Returns the label and updates s; all lanes of all W
+// wavefronts return the same values.
+template <int MODE, int W, bool SPLIT, class Index>
+__device__ __forceinline__ int greedy_step(const DevTrie &t, const Index &ci, const LdsAsr<W> &asr, float rowV,
+                                           float lambda, int &s, int pv, float *ls, int *ln, Exchange *xc, int &xi,
+                                           int wave, int lane) {
     const int V = t.vocab_size;
     const float fin = MODE == kAed ? t.final_w[s] : 0.0f;   // <eos> takes the state's final weight
     // The chain record is fetched first: in CTC and transducer modes its load
     // overlaps the plain ASR argmax, which may still find that the LM is not needed.
     int nlev;
-    if (ROW_PENDING) memory_order_point();   // the ASR row's copies were issued before the record load
+    memory_order_point();   // the ASR row's copies were issued before the record load
     const int4 rec = fetch_record(t, ci, s, lane, nlev);
-    after_record();
     if (MODE == kCtc || MODE == kTransducer) {
-        // the row, not the record: the record load (one instruction; after_record
-        // adds none when the row is pending) stays in flight through the argmax
-        if (ROW_PENDING) wait_lds_copies_but_last();
+        // the row, not the record: the record load (one instruction) stays in
+        // flight through the argmax
+        wait_lds_copies_but_last();
         float bx = -__builtin_inff(), av;
         int bi = kNone, unused;
         asr.argmax(V, wave, lane, bx, bi);
         int a = group_argmax<W>(bx, bi, 0, av, unused, xc, xi, wave, lane);
         if (a == kNone) a = 0;                    // every token at -inf: the first one, unless blank beats it
         if (rowV > av) a = V;                     // blank only when strictly larger (it has the highest index)
-        if (a == V || (MODE == kCtc && a == pv)) {   // blank or repeat: no LM, no move
-            if (pf_src) copy_stripes_dword<W>(pf_src, pf_dst, pf_n, wave, lane);
-            return a;
-        }
+        if (a == V || (MODE == kCtc && a == pv)) return a;   // blank or repeat: no LM, no move
     }
-    const ChainHead h = walk_record<W, SPLIT>(t, rec, nlev, ls, ln, lane, wave, pf_src, pf_dst, pf_n);
+    const ChainHead h = walk_record<W, SPLIT>(t, rec, nlev, ls, ln, lane, wave);
     // CTC: the previous label is no candidate; its slot reads NaN, which no
     // fused value built from it can pass under a strict '>'
     if (MODE == kCtc && pv >= 0 && pv < V && owns_token<W>(pv, wave) && lane == 0) {
@@ -368,49 +209,6 @@ __device__ __forceinline__ int greedy_step(const DevTrie &t, const Index &ci, co
         ns = first_token_state<W>(h, ls, ln, w, xc, xi, wave, lane);
     }
     s = ns;
-    return w;
-}
-
-// The same step for the whole decode with rows in registers and compact
-// dense rows (W = 1): the walk applies the sparse levels only, over cleared
-// marks, and the dense row arrives in registers; the winner's next state
-// follows from the compact row's rules.  Same selection as greedy_step.
-template <int MODE, bool FULL, class AfterRecord>
-__device__ __forceinline__ int greedy_step_compact(const DevTrie &t, const ChainIndex &ci,
-                                                   const RegAsr<1, FULL> &asr, float rowV, float lambda, int &s,
-                                                   int pv, float *ls, int *ln, Exchange *xc, int &xi, int lane,
-                                                   AfterRecord after_record) {
-    const int V = t.vocab_size;
-    const float fin = MODE == kAed ? t.final_w[s] : 0.0f;
-    int nlev;
-    const int4 rec = fetch_record(t, ci, s, lane, nlev);
-    after_record();
-    if (MODE == kCtc || MODE == kTransducer) {
-        float bx = -__builtin_inff(), av;
-        int bi = kNone, unused;
-        asr.argmax(V, 0, lane, bx, bi);
-        int a = group_argmax<1>(bx, bi, 0, av, unused, xc, xi, 0, lane);
-        if (a == kNone) a = 0;
-        if (rowV > av) a = V;
-        if (a == V || (MODE == kCtc && a == pv)) return a;
-    }
-    const ChainHead h = head_of(rec);
-    clear_marks(ln, V, lane);
-    CompactRow<FULL> row;
-    row.load(t.dense_c + size_t(h.dense_row) * size_t(V), V, lane);
-    const int base = t.dense_base[h.dense_row];
-    walk_record<1, false, true>(t, rec, nlev, ls, ln, lane);
-    if (MODE == kCtc && pv >= 0 && pv < V && lane == 0) {
-        ls[pv] = __builtin_nanf("");
-        ln[pv] = kFinal;
-    }
-    float bx = -__builtin_inff(), wv;
-    int bi = kNone, unused;
-    row.fused(h, ls, ln, asr, lambda, V, lane, bx, bi);
-    int w = group_argmax<1>(bx, bi, 0, wv, unused, xc, xi, 0, lane);
-    if (MODE == kAed && __builtin_fmaf(lambda, fin, rowV) > wv) return V;
-    if (w == kNone) w = (MODE == kCtc && pv == 0) ? 1 : 0;   // every candidate at -inf: the first one
-    s = row.next_state(t, ln, base, w, V, lane);
     return w;
 }
 
@@ -461,138 +259,12 @@ __global__ __launch_bounds__(W * kWave) void fused_step_kernel(DevTrie t, const 
     int xi = 0;
     // every wavefront has read states[b] and prev[b] before the first exchange
     // barrier inside the step, and wavefront 0 writes them back after it
-    const int label = greedy_step<MODE, W, true, LdsAsr<W>, NoHook, SPLIT>(
+    const int label = greedy_step<MODE, W, SPLIT>(
         t, ci, LdsAsr<W>{arow}, rowV, lambda, s, pv, ls, ln, xc, xi, wave, lane);
     if (wave == 0 && lane == 0) {
         tokens[b] = label;
         states[b] = s;
         if (MODE == kCtc) prev[b] = label;
-    }
-}
-
-// Whole greedy decode: utterance b runs frames 0 .. len_b - 1 of
-// asr[b * stride_b + t * stride_t + class]; one utterance per workgroup of W
-// wavefronts.  NB: ASR row buffers in LDS (1 or 2), or 0 for rows held in
-// registers (V <= kRegTokens; FULL: V = kRegTokens).
-template <int MODE, int W, int NB, bool FULL = false, bool SPLIT = false, bool COMPACT = false>
-__global__ __launch_bounds__(W * kWave) void fused_decode_kernel(DevTrie t, const float *__restrict__ asr, int64_t B,
-                                                                  int64_t T, int64_t stride_b, int64_t stride_t,
-                                                                  const int32_t *__restrict__ lengths, float lambda,
-                                                                  int32_t *__restrict__ states,
-                                                                  int32_t *__restrict__ prev,
-                                                                  int32_t *__restrict__ labels,
-                                                                  int32_t *__restrict__ label_states) {
-    extern __shared__ float lds[];
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int lane = threadIdx.x % kWave;
-    const int64_t b = blockIdx.x;
-    if (b >= B) return;
-    const int V = t.vocab_size;
-    const int rowp = asr_row_words(V);
-    // ASR rows: NB = 2 buffers, the next row's copy riding along with the walk
-    // (while every utterance is resident at once, the latency-bound case), or
-    // NB = 1 buffer, refilled once the frame has read it (when more utterances
-    // than fit wait for a CU: the smaller LDS footprint lets more run at once),
-    // or in registers (NB = 0), the next row loaded behind the chain record
-    constexpr int kRowBufs = NB;
-    RegAsr<W, FULL> cur_r;
-    float *ls = lds;
-    int *ln = reinterpret_cast<int *>(ls + lds_row(V));
-    float *abuf = reinterpret_cast<float *>(ln + lds_row(V));
-    Exchange *xc = reinterpret_cast<Exchange *>(abuf + kRowBufs * rowp);
-    int32_t *lab = labels + b * T;
-    int32_t *lst = label_states ? label_states + b * T : nullptr;
-
-    int64_t len = T;
-    if (lengths) {
-        len = __builtin_amdgcn_readfirstlane(lengths[b]);
-        len = len < 0 ? 0 : (len > T ? T : len);
-    }
-    int s = __builtin_amdgcn_readfirstlane(states[b]);
-    if (s < 0 || s >= t.num_states) {
-        if (wave == 0) {
-            if (lane == 0) atomicAdd(&t.status[0], 1);
-            for (int64_t f = lane; f < T; f += kWave) {
-                lab[f] = -1;
-                if (lst) lst[f] = -1;
-            }
-        }
-        return;
-    }
-    int pv = MODE == kCtc ? __builtin_amdgcn_readfirstlane(prev[b]) : -1;
-    const float *row = asr + b * stride_b;
-    if (len > 0) {
-        if (kRowBufs == 0)
-            cur_r.load(row, V, wave, lane);
-        else
-            copy_stripes_dword<W>(row, abuf, V, wave, lane);
-    }
-    float rowV = (MODE != kPlain && len > 0) ? row[V] : 0.0f;
-    int keep_lab = -1, keep_st = -1, xi = 0;
-    const ChainIndex ci = chain_index(t, lane);
-    for (int64_t f = 0; f < len; ++f, row += stride_t) {
-        // LDS rows: frame f reads its ASR row from LDS, copied during frame
-        // f - 1 (or before the loop); the walk also starts the copy of row
-        // f + 1.  (The wait comes before any load of this frame is issued.)
-        if (kRowBufs > 0) wait_lds_copies();
-        const bool more = f + 1 < len;
-        const float *pf = more ? row + stride_t : nullptr;
-        const float next_v = (MODE != kPlain && more) ? row[stride_t + V] : 0.0f;
-        int label;
-        if constexpr (kRowBufs == 0) {
-            // the last frame reloads its own row: with no branch around the
-            // loads the compiler's count of loads in flight stays exact
-            RegAsr<W, FULL> nxt_r;
-            const float *src = more ? pf : row;
-            auto load_next = [&]() { nxt_r.load(src, V, wave, lane); };
-            if constexpr (COMPACT) {
-                static_assert(W == 1, "compact dense rows serve one wavefront per utterance");
-                label = greedy_step_compact<MODE, FULL>(t, ci, cur_r, rowV, lambda, s, pv, ls, ln, xc, xi, lane,
-                                                        load_next);
-            } else {
-                label = greedy_step<MODE, W, false, RegAsr<W, FULL>, decltype(load_next), SPLIT>(
-                    t, ci, cur_r, rowV, lambda, s, pv, ls, ln, xc, xi, wave, lane, nullptr, nullptr, 0, load_next);
-            }
-            cur_r = nxt_r;
-        } else {
-            float *cur = abuf + (kRowBufs == 2 ? (f & 1) * rowp : 0);
-            float *nxt = abuf + (kRowBufs == 2 ? ((f + 1) & 1) * rowp : 0);
-            label = greedy_step<MODE, W, false, LdsAsr<W>, NoHook, SPLIT>(
-                t, ci, LdsAsr<W>{cur}, rowV, lambda, s, pv, ls, ln, xc, xi, wave, lane, kRowBufs == 2 ? pf : nullptr,
-                nxt, V);
-            // one buffer: every read of this frame's row has completed (its values
-            // were consumed by the argmax), so the next row can be copied over it
-            if (kRowBufs == 1 && pf) copy_stripes_dword<W>(pf, cur, V, wave, lane);
-        }
-        rowV = next_v;
-        if (MODE == kCtc) pv = label;
-        // Lane f % 64 of wavefront 0 keeps frame f's label and state; one
-        // coalesced store per 64 frames, so the wait at the top of a frame
-        // rarely has a store to drain.
-        const int slot = int(f & (kWave - 1));
-        if (lane == slot) {
-            keep_lab = label;
-            keep_st = s;
-        }
-        if (wave == 0 && (slot == kWave - 1 || f + 1 == len)) {
-            const int64_t f0 = f - slot;
-            if (lane <= slot) {
-                lab[f0 + lane] = keep_lab;
-                if (lst) lst[f0 + lane] = keep_st;
-            }
-        }
-    }
-    if (wave == 0) {
-        for (int64_t f = len + lane; f < T; f += kWave) {   // frames past the utterance's end
-            lab[f] = -1;
-            if (lst) lst[f] = s;
-        }
-        // every wavefront read states[b] and prev[b] before the first exchange
-        // barrier; with no frame at all the values written are the ones read
-        if (lane == 0) {
-            states[b] = s;
-            if (MODE == kCtc) prev[b] = pv;
-        }
     }
 }
 
@@ -968,12 +640,6 @@ hipError_t launch_fused_topk(const DevTrie &t, const float *asr, int64_t B, int6
     return hipGetLastError();
 }
 
-// Wavefronts per hypothesis: a batch of up to 512 hypotheses leaves most SIMDs
-// idle with one wavefront each, so each hypothesis gets four (measured on the
-// 20M 6-gram decode: 4-12 % less time per frame); from 1024 on, one wavefront
-// per hypothesis keeps more work in flight and wins.
-inline int waves_per_hyp(int64_t B) { return B <= 512 ? 4 : 1; }
-
 // The same choice for one step per launch, where every launch pays the whole
 // dependent chain once: four wavefronts stay ahead up to 1024 hypotheses
 // (20M 6-gram, CTC: 8.54 against 8.70 us per step at 768, 8.95 against 9.12
@@ -1018,108 +684,6 @@ hipError_t launch_fused_step(const DevTrie &t, const float *asr, int64_t B, int6
         case kCtc: return launch_step_mode<kCtc>(t, asr, B, ld, lambda, states, prev, tokens, stream);
         case kAed: return launch_step_mode<kAed>(t, asr, B, ld, lambda, states, prev, tokens, stream);
         default: return launch_step_mode<kTransducer>(t, asr, B, ld, lambda, states, prev, tokens, stream);
-    }
-}
-
-template <int MODE, int W, int NB, bool FULL = false>
-static hipError_t launch_decode_w(const DevTrie &t, const float *asr, int64_t B, int64_t T, int64_t sb, int64_t st,
-                                  const int32_t *lengths, float lambda, int32_t *states, int32_t *prev,
-                                  int32_t *labels, int32_t *label_states, hipStream_t stream) {
-    if constexpr (W > 1) {
-        if (stripe_split<W>(t)) {
-            hipLaunchKernelGGL((fused_decode_kernel<MODE, W, NB, FULL, true>), dim3(unsigned(B)), dim3(W * kWave),
-                               hyp_lds_bytes(t.vocab_size, NB), stream, t, asr, B, T, sb, st, lengths, lambda, states,
-                               prev, labels, label_states);
-            return hipGetLastError();
-        }
-    }
-    if constexpr (W == 1 && NB == 0) {
-        if (t.dense_c) {
-            hipLaunchKernelGGL((fused_decode_kernel<MODE, 1, 0, FULL, false, true>), dim3(unsigned(B)), dim3(kWave),
-                               hyp_lds_bytes(t.vocab_size, 0), stream, t, asr, B, T, sb, st, lengths, lambda, states,
-                               prev, labels, label_states);
-            return hipGetLastError();
-        }
-    }
-    hipLaunchKernelGGL((fused_decode_kernel<MODE, W, NB, FULL, false>), dim3(unsigned(B)), dim3(W * kWave),
-                       hyp_lds_bytes(t.vocab_size, NB), stream, t, asr, B, T, sb, st, lengths, lambda, states, prev,
-                       labels, label_states);
-    return hipGetLastError();
-}
-
-// Utterances the device holds at once with two ASR row buffers per utterance
-// (one wavefront each): CUs times the workgroups whose LDS fits one CU.  The
-// two device attributes are queried once per device and kept (a decode call
-// then costs one hipGetDevice on the host for this).
-static int64_t resident_double_buffered(const DevTrie &t) {
-    constexpr int kMaxDevices = 64;
-    static std::atomic<int64_t> cached[kMaxDevices];   // CUs << 32 | LDS bytes per CU; 0: not yet known
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0) {
-        (void)hipGetLastError();
-        return INT64_MAX;   // unknown: keep two buffers
-    }
-    int64_t c = dev < kMaxDevices ? cached[dev].load(std::memory_order_relaxed) : 0;
-    if (c == 0) {
-        int cus = 0, lds = 0;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) != hipSuccess ||
-            cus <= 0 || lds <= 0) {
-            (void)hipGetLastError();
-            return INT64_MAX;
-        }
-        c = (int64_t(cus) << 32) | int64_t(uint32_t(lds));
-        if (dev < kMaxDevices) cached[dev].store(c, std::memory_order_relaxed);
-    }
-    const int64_t cus = c >> 32, lds = c & 0xffffffff;
-    return cus * int64_t(size_t(lds) / hyp_lds_bytes(t.vocab_size, 2));
-}
-
-template <int MODE>
-static hipError_t launch_decode_mode(const DevTrie &t, const float *asr, int64_t B, int64_t T, int64_t sb,
-                                     int64_t st, const int32_t *lengths, float lambda, int32_t *states,
-                                     int32_t *prev, int32_t *labels, int32_t *label_states, hipStream_t stream) {
-    if (waves_per_hyp(B) == 4)
-        return launch_decode_w<MODE, 4, 2>(t, asr, B, T, sb, st, lengths, lambda, states, prev, labels, label_states,
-                                           stream);
-    // Measured on the 20M 6-gram, CTC, 200 frames: with compact dense rows
-    // the register rows are the fastest at every size (0.556 / 0.571 / 0.611
-    // / 0.625 / 0.654 ms against 0.624 / 0.638 / 0.696 / 0.705 / 0.789 ms for
-    // two LDS row buffers at 600 / 1024 / 1536 / 2048 / 2304 utterances).
-    // Without them: while every utterance is resident with two LDS row
-    // buffers (2304 utterances on 256 CUs at V = 1024), those are 2-4 % faster
-    // than rows in registers; beyond that the register rows (up to 16
-    // utterances per CU) are 27 % faster at 4096 utterances and 18 % at 8192,
-    // and one LDS buffer (13 per CU) still beats two by 8-14 %.
-    if (!(t.dense_c && t.vocab_size <= kRegTokens) && B <= resident_double_buffered(t))
-        return launch_decode_w<MODE, 1, 2>(t, asr, B, T, sb, st, lengths, lambda, states, prev, labels, label_states,
-                                           stream);
-    if (t.vocab_size == kRegTokens)
-        return launch_decode_w<MODE, 1, 0, true>(t, asr, B, T, sb, st, lengths, lambda, states, prev, labels,
-                                                 label_states, stream);
-    if (t.vocab_size < kRegTokens)
-        return launch_decode_w<MODE, 1, 0>(t, asr, B, T, sb, st, lengths, lambda, states, prev, labels, label_states,
-                                           stream);
-    return launch_decode_w<MODE, 1, 1>(t, asr, B, T, sb, st, lengths, lambda, states, prev, labels, label_states,
-                                       stream);
-}
-
-hipError_t launch_fused_decode(const DevTrie &t, const float *asr, int64_t B, int64_t T, int64_t sb, int64_t st,
-                               const int32_t *lengths, int mode, float lambda, int32_t *states, int32_t *prev,
-                               int32_t *labels, int32_t *label_states, hipStream_t stream) {
-    switch (mode) {
-        case kPlain:
-            return launch_decode_mode<kPlain>(t, asr, B, T, sb, st, lengths, lambda, states, prev, labels,
-                                              label_states, stream);
-        case kCtc:
-            return launch_decode_mode<kCtc>(t, asr, B, T, sb, st, lengths, lambda, states, prev, labels,
-                                            label_states, stream);
-        case kAed:
-            return launch_decode_mode<kAed>(t, asr, B, T, sb, st, lengths, lambda, states, prev, labels,
-                                            label_states, stream);
-        default:
-            return launch_decode_mode<kTransducer>(t, asr, B, T, sb, st, lengths, lambda, states, prev, labels,
-                                                   label_states, stream);
     }
 }
 

@@ -365,15 +365,12 @@ __device__ __forceinline__ void apply_level(const DevTrie &t, int a0, int end, f
 // The walk of a fetched record into (ls, ln), the stripes of wavefront `wave`
 // of W (SPLIT: each wavefront owns exactly one stripe, and loads only its part
 // of each level; HALVES: two wavefronts, each owning one 512-token half).
-// When pf_src is given, pf_n words from it are also copied into pf_dst (the
-// owned stripes) once the record is in (a prefetch that rides along with the
-// dense row and the arcs).  DENSE_ISSUED: the caller already issued the copy
+// DENSE_ISSUED: the caller already issued the copy
 // of the dense row (before any arc load, which orders the arcs' LDS writes
 // after it).
 template <int W = 1, bool SPLIT = false, bool DENSE_ISSUED = false, bool HALVES = false>
 __device__ __forceinline__ ChainHead walk_record(const DevTrie &t, const int4 &rec, int nlev, float *ls, int *ln,
-                                                 int lane, int wave = 0, const float *pf_src = nullptr,
-                                                 float *pf_dst = nullptr, int pf_n = 0) {
+                                                 int lane, int wave = 0) {
     const ChainHead h = head_of(rec);
     if (!DENSE_ISSUED) {
         if (HALVES)
@@ -381,7 +378,6 @@ __device__ __forceinline__ ChainHead walk_record(const DevTrie &t, const int4 &r
         else
             dense_stripes_to_lds<W>(t, h.dense_row, ls, ln, wave, lane);
     }
-    if (pf_src) copy_stripes_dword<W>(pf_src, pf_dst, pf_n, wave, lane);
     for (int j = nlev; j >= 1; --j) {
         int a0, end;
         level_bounds<W, SPLIT, HALVES>(rec, j, wave, a0, end);
