@@ -1,9 +1,10 @@
 // Device pieces shared by the fused kernels (step, whole decode, top-k).
 //
-// A hypothesis is held by a group of W wavefronts, one workgroup.  Wavefront w
-// owns the tokens [64 NT w, 64 NT (w + 1)), lane l of it the NT tokens 64 i + l
-// of that range: their ASR scores and the dense row's entries sit in registers
-// (one coalesced 256-byte load per 64 tokens).  Only the sparse levels go
+// A hypothesis is held by a group of W wavefronts, one workgroup.  The tokens
+// are dealt to the wavefronts in ranges of whole 64-token tiles, at most NT
+// tiles each; lane l of a wavefront owns tokens 64 i + l of its range: their
+// ASR scores and the dense row's entries sit in registers (one coalesced
+// 256-byte load per tile).  Only the sparse levels go
 // through LDS, one 8-byte slot {score, next state | kFinal} per token, all
 // zero where no level holds the token; a wavefront writes and reads its own
 // slots only, so the group needs no barrier for the walk.
@@ -49,9 +50,9 @@ __device__ __forceinline__ int lane_zero() {
 template <int NT>
 struct Words {
     int v[NT];
-    // words lane, lane + 64, ... of the n words at p (n may be <= 0); 0 past them
+    // words lane, lane + 64, ... of the n >= 0 words at p; 0 past them
     __device__ __forceinline__ void load(const void *p, int n, int lane) {
-        const __amdgpu_buffer_rsrc_t r = word_buffer(p, n > 0 ? n : 0);
+        const __amdgpu_buffer_rsrc_t r = word_buffer(p, n);
         int at = lane * 4;
         asm volatile("" : "+v"(at));   // or the NT offsets are hoisted into registers of their own
 #pragma unroll
@@ -209,22 +210,27 @@ __device__ __forceinline__ int winner_entry(unsigned key, int tok) {
 template <int W, int NT, bool FULL>
 struct Group {
     static constexpr int kRange = kWave * NT;
+    static_assert(NT % 2 == 0, "slots are cleared two at a time");
     // each wavefront's range starts and ends at a multiple of 256: it loads only
     // its part of every level where the levels carry split counts
     static constexpr bool kSplit = W > 1 && W * kRange <= kSplitVocab && NT % 4 == 0;
     static constexpr bool kFilter = W > 1 && !kSplit;
 
-    int wave, lane, t0, own;   // own: tokens of this wavefront (none if <= 0)
-    i32x2 *slots;
+    int wave, lane;
+    int range;                 // tokens dealt to each wavefront but the last ones
+    int t0, own;               // first token, tokens of this wavefront (none past V)
+    i32x2 *slots;              // of this wavefront: slot of token t at t - t0
     int sh0, sh1;              // split counts below the range's two ends: shift
     unsigned mk0, mk1;         // and mask (0: none below the first, all below the last)
 
     __device__ __forceinline__ Group(int V, i32x2 *all_slots) {
         wave = W == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
         lane = threadIdx.x % kWave;
-        t0 = kRange * wave;
-        own = V - t0 < kRange ? V - t0 : kRange;
-        slots = all_slots + t0;
+        // split counts fix the ranges' ends; otherwise every wavefront gets its share
+        range = FULL || kSplit || W == 1 ? kRange : ((V + kWave - 1) / kWave + W - 1) / W * kWave;
+        t0 = range * wave;
+        own = min(max(V - t0, 0), range);
+        slots = all_slots + kRange * wave;
         const int q0 = wave * NT / 4, q1 = (wave + 1) * NT / 4;
         sh0 = q0 == 1 ? 0 : (q0 == 2 ? 9 : 19);
         sh1 = q1 == 1 ? 0 : (q1 == 2 ? 9 : 19);
@@ -247,7 +253,6 @@ struct Group {
         const i32x4 z = {0, 0, 0, 0};
 #pragma unroll
         for (int i = 0; i < NT / 2; ++i) reinterpret_cast<i32x4 *>(slots)[kWave * i + lane] = z;
-        if (NT == 1) slots[lane] = i32x2{0, 0};
     }
     // The record's sparse levels into the slots, order 2 first, so that the
     // highest order holding a token is the last to write it (LDS operations of
@@ -268,9 +273,9 @@ struct Group {
             if (n == 0) continue;
             any = true;
             if (j == 1 && top)
-                put_arcs<true, kFilter>(t, a0, n, acc, slots, t0, kRange, lane);
+                put_arcs<true, kFilter>(t, a0, n, acc, slots, t0, own, lane);
             else
-                put_arcs<false, kFilter>(t, a0, n, acc, slots, t0, kRange, lane);
+                put_arcs<false, kFilter>(t, a0, n, acc, slots, t0, own, lane);
         }
         return any;
     }
