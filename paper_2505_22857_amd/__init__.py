@@ -2,7 +2,8 @@
 
 A thin ctypes binding of ``libngpu_lm.so`` (C ABI in ``include/ngpu_lm.h``).
 Every step of a query runs in the library's HIP kernels; this module only
-marshals arguments.  PyTorch supplies device memory and the current HIP
+marshals arguments, for the per-frame calls through the small native module
+``_fastcall.so`` (``csrc/fastcall.cpp``).  PyTorch supplies device memory and the current HIP
 stream.  The library must be built first (``__graft_entry__.build()`` or
 ``python -m paper_2505_22857_amd.build``); without it every call raises.
 """
@@ -17,6 +18,7 @@ import numpy as np
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libngpu_lm.so")
+FAST_PATH = os.path.join(HERE, "_fastcall.so")
 
 NGPU_FUSION_PLAIN, NGPU_FUSION_CTC, NGPU_FUSION_TRANSDUCER, NGPU_FUSION_AED = 0, 1, 2, 3
 NGPU_BUILD_BOS_EOS = 1
@@ -104,6 +106,30 @@ def load_library(path: str = LIB_PATH):
             getattr(lib, name).restype = ctypes.c_int
     _lib = lib
     return lib
+
+
+_fast = None
+
+
+def _load_fast():
+    """The native per-call module, bound to the loaded library; raises if it has not been built."""
+    global _fast
+    if _fast is None:
+        import importlib.machinery
+        import importlib.util
+
+        import torch  # noqa: F401  (the module links against torch's libraries)
+        if not os.path.exists(FAST_PATH):
+            raise RuntimeError(f"{FAST_PATH} is missing: build it with __graft_entry__.build()")
+        name = __name__ + "._fastcall"
+        loader = importlib.machinery.ExtensionFileLoader(name, FAST_PATH)
+        mod = importlib.util.module_from_spec(importlib.util.spec_from_loader(name, loader))
+        loader.exec_module(mod)
+        lib = load_library()
+        mod.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in
+                   (lib.ngpu_lm_advance, lib.ngpu_lm_fused_greedy_step, lib.ngpu_lm_fused_topk)))
+        _fast = mod
+    return _fast
 
 
 def _check(rc: int):
@@ -208,6 +234,7 @@ class NgpuLM:
         _check(self._lib.ngpu_lm_start_state(h, ctypes.byref(st)))
         self.start_state = int(st.value)
         self._dev = None
+        self._fast = None
 
     @classmethod
     def from_model(cls, model, shuffle_seed: Optional[int] = None):
@@ -229,6 +256,7 @@ class NgpuLM:
     def upload(self, device="cuda", stream=None):
         """Allocate the device image with torch and copy the trie into it."""
         import torch
+        self._fast = _load_fast()
         buf = torch.empty(self.device_bytes + 256, dtype=torch.uint8, device=device)
         off = (-buf.data_ptr()) % 256
         view = buf[off:off + self.device_bytes]
@@ -241,6 +269,12 @@ class NgpuLM:
 
     def advance(self, states, scores=None, next_states=None, stream=None):
         """Scores [B, V] fp32 and next states [B, V] int32 for device int32 ``states`` [B]."""
+        if stream is None and self._fast is not None:
+            r = self._fast.advance(self._h.value, self.vocab_size, states, scores, next_states)
+            if r is not None:   # None: not the ordinary call, handled (or refused) below
+                if r.__class__ is int:
+                    _check(r)
+                return r
         import torch
         B = states.numel()
         if scores is None:
@@ -262,6 +296,12 @@ class NgpuLM:
     def fused_greedy_step(self, asr, lam: float, states, prev=None, mode: int = NGPU_FUSION_PLAIN,
                           tokens=None, stream=None):
         """One greedy fusion step; ``states`` (and ``prev`` for CTC) are updated in place."""
+        if stream is None and self._fast is not None:
+            r = self._fast.step(self._h.value, self.vocab_size, asr, lam, states, prev, mode, tokens)
+            if r is not None:
+                if r.__class__ is int:
+                    _check(r)
+                return r
         import torch
         if asr.dim() != 2 or asr.stride(1) != 1:
             raise TypeError("asr must be a [B, ld] tensor with unit stride in the last dimension")
@@ -298,6 +338,12 @@ class NgpuLM:
                    stream=None):
         """k best fused tokens per hypothesis: (tokens int32, scores fp32, next states int32), each [B, k]
         (allocated unless given)."""
+        if stream is None and self._fast is not None:
+            r = self._fast.topk(self._h.value, self.vocab_size, asr, lam, k, states, tokens, scores, next_states)
+            if r is not None:
+                if r.__class__ is int:
+                    _check(r)
+                return r
         import torch
         if asr.dim() != 2 or asr.stride(1) != 1 or asr.dtype != torch.float32 or not asr.is_cuda:
             raise TypeError("asr must be a float32 [B, ld] device tensor with unit stride in the last dimension")
