@@ -71,7 +71,7 @@ __global__ __launch_bounds__(W * kWave) void topk_kernel(DevTrie t, const float 
     const int4 rec = load_record(ri, s, lane);
     const ChainHead h = head_of(rec);
     g.load_dense(t, unsigned(h.dense_row), dw, dt);
-    const bool any = g.put_levels(t, rec, h);
+    const bool any = g.template put_levels<true>(t, rec, h);
     float x[NT];
     int nx[NT];
     unsigned key[NT];
