@@ -18,8 +18,13 @@
 
 namespace ngpu {
 
+// How the ASR rows are loaded: as usual, or non-temporally, so that a stream
+// larger than the 256 MB Infinity Cache leaves the dense rows, records and arcs
+// in the caches.
+constexpr int kKeep = 0, kStream = 2;   // aux bits of a buffer load: nt = 2
+
 // W wavefronts per utterance, or one whose tokens are few (NT <= 8).
-template <int MODE, int W, int NT, bool FULL>
+template <int MODE, int W, int NT, bool FULL, int CACHE>
 __global__ __launch_bounds__(W * kWave) void decode_kernel(DevTrie t, int uni_base, const float *__restrict__ asr,
                                                            int64_t T, int64_t stride_t, int64_t stride_b,
                                                            const int32_t *__restrict__ lengths, float lambda,
@@ -59,7 +64,7 @@ __global__ __launch_bounds__(W * kWave) void decode_kernel(DevTrie t, int uni_ba
     Words<NT> cur, nxt, nn, dw, dt;
     float cur_v = 0.0f, nxt_v = 0.0f, nn_v = 0.0f, fin = 0.0f;
     auto load_row = [&](const float *row, Words<NT> &x, float &v) {
-        g.load_row(row, x);
+        g.template load_row<CACHE>(row, x);
         if (MODE != kPlain) v = row[V + zero];   // blank or <eos>
     };
     int4 rec;
@@ -263,9 +268,10 @@ __device__ __forceinline__ int pick(const Words<NT> &x, int j, int l) {
 // plain argmax needs the row's maximum only (three-input maxima): blank is
 // above it or not, and a repeat is the previous label holding it; the winner's
 // token is searched where the wave's maximum is found.  4096 utterances x 200
-// frames, V = 1024: 820 us, of which the ASR rows alone (3.36 GB) take 670 at
-// the rate of a copy; V = 700, 100 frames: 325 us.
-template <int MODE, int NT, bool FULL, bool COMPACT>
+// frames, V = 1024: 782 us (820 in the kernel before, 8-byte slots and one frame's
+// chain in line); without any LM work the stream of ASR rows (3.36 GB) alone takes
+// 670.  V = 700, 100 frames: 329 us (673 before).
+template <int MODE, int NT, bool FULL, bool COMPACT, int CACHE>
 __global__ __launch_bounds__(kWave, (COMPACT ? 4 : 1)) void decode_wave_kernel(
     DevTrie t, int uni_base, const float *__restrict__ asr, int64_t T, int64_t stride_t, int64_t stride_b,
     const int32_t *__restrict__ lengths, float lambda, int32_t *__restrict__ states, int32_t *__restrict__ prev,
@@ -299,7 +305,7 @@ __global__ __launch_bounds__(kWave, (COMPACT ? 4 : 1)) void decode_wave_kernel(
     Words<NT> bufa, bufb;
     float va = 0.0f, vb = 0.0f;
     auto load_row = [&](const float *row, Words<NT> &x, float &v) {
-        x.load(row, V, lane);
+        x.template load<CACHE>(row, V, lane);
         if (MODE != kPlain) v = row[V + zero];
     };
     int4 rec;
@@ -447,44 +453,69 @@ __global__ __launch_bounds__(kWave, (COMPACT ? 4 : 1)) void decode_wave_kernel(
     }
 }
 
+// A launch's arguments.
+struct Decode {
+    DevTrie t;
+    int uni_base;
+    const float *asr;
+    int64_t B, T, sb, st;
+    const int32_t *lengths;
+    float lambda;
+    int32_t *states, *prev, *labels, *label_states;
+    hipStream_t stream;
+    // The ASR rows outgrow the Infinity Cache: stream them.  us a launch, kept
+    // against streamed: 1.05 GB (256 x 1000, 20M 6-gram) 1827 / 1712, 3.4 GB (4096 x
+    // 200) 811 / 782, 615 MB (1000 x 150, V = 1024) 306 / 300; 246 MB (300 x 200)
+    // 327 / 327; 216 MB (600 x 60, V = 1500) 137 / 144, 48 MB (40 x 200) 295 / 325:
+    // a smaller tensor may still be cached from its writer.
+    bool streams() const {
+        const double row = 4.0 * (t.vocab_size + 1);
+        return double(B) * double(T) * row > 256.0 * (1 << 20);
+    }
+};
+
 // A grid holds at most 2^32 - 1 work-items: larger batches go in several launches.
-template <int MODE, int W, int NT>
-static hipError_t launch_group(const DevTrie &t, int uni_base, const float *asr, int64_t B, int64_t T, int64_t sb,
-                               int64_t st, const int32_t *lengths, float lambda, int32_t *states, int32_t *prev,
-                               int32_t *labels, int32_t *label_states, hipStream_t stream) {
+template <int MODE, int W, int NT, bool FULL, int CACHE>
+static hipError_t launch_group(const Decode &d) {
     constexpr int64_t kMost = int64_t(UINT32_MAX) / (W * kWave);
     const size_t lds = sizeof(Meet) + size_t(W) * kWave * NT * sizeof(i32x2);
-    const dim3 block(W * kWave);
-    for (int64_t b0 = 0; b0 < B; b0 += kMost) {
-        const dim3 grid{unsigned(B - b0 < kMost ? B - b0 : kMost)};
-        const float *a = asr + b0 * sb;
-        const int32_t *ln = lengths ? lengths + b0 : nullptr;
-        int32_t *pv = prev ? prev + b0 : nullptr, *ls = label_states ? label_states + b0 * T : nullptr;
-        if (t.vocab_size == W * kWave * NT)
-            hipLaunchKernelGGL((decode_kernel<MODE, W, NT, true>), grid, block, lds, stream, t, uni_base, a, T, st, sb,
-                               ln, lambda, states + b0, pv, labels + b0 * T, ls);
-        else
-            hipLaunchKernelGGL((decode_kernel<MODE, W, NT, false>), grid, block, lds, stream, t, uni_base, a, T, st, sb,
-                               ln, lambda, states + b0, pv, labels + b0 * T, ls);
+    for (int64_t b0 = 0; b0 < d.B; b0 += kMost) {
+        const dim3 grid{unsigned(d.B - b0 < kMost ? d.B - b0 : kMost)};
+        hipLaunchKernelGGL((decode_kernel<MODE, W, NT, FULL, CACHE>), grid, dim3(W * kWave), lds, d.stream, d.t,
+                           d.uni_base, d.asr + b0 * d.sb, d.T, d.st, d.sb, d.lengths ? d.lengths + b0 : nullptr, d.lambda,
+                           d.states + b0, d.prev ? d.prev + b0 : nullptr, d.labels + b0 * d.T,
+                           d.label_states ? d.label_states + b0 * d.T : nullptr);
         if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
-template <int MODE, bool FULL>
-static hipError_t launch_wave(const DevTrie &t, int uni_base, const float *asr, int64_t B, int64_t T, int64_t sb,
-                              int64_t st, const int32_t *lengths, float lambda, int32_t *states, int32_t *prev,
-                              int32_t *labels, int32_t *label_states, hipStream_t stream) {
+// Rows of up to 512 tokens are always kept: streamed, V = 128 took 143 against
+// 136 us at 1500 utterances, 178 against 165 at 4000 (two rows share a line).
+template <int MODE, int W, int NT>
+static hipError_t launch_group(const Decode &d) {
+    const bool full = d.t.vocab_size == W * kWave * NT;
+    if constexpr (W > 1) {
+        if (d.streams())
+            return full ? launch_group<MODE, W, NT, true, kStream>(d) : launch_group<MODE, W, NT, false, kStream>(d);
+    }
+    return full ? launch_group<MODE, W, NT, true, kKeep>(d) : launch_group<MODE, W, NT, false, kKeep>(d);
+}
+
+template <int MODE, bool FULL, bool COMPACT, int CACHE>
+static hipError_t launch_wave(const Decode &d) {
     constexpr int NT = 16;
-    const size_t lds = size_t(kWave) * NT * sizeof(i32x2);
-    const dim3 grid{unsigned(B)}, block(kWave);
-    if (t.dense_c)
-        hipLaunchKernelGGL((decode_wave_kernel<MODE, NT, FULL, true>), grid, block, lds, stream, t, uni_base, asr, T, st,
-                           sb, lengths, lambda, states, prev, labels, label_states);
-    else
-        hipLaunchKernelGGL((decode_wave_kernel<MODE, NT, FULL, false>), grid, block, lds, stream, t, uni_base, asr, T,
-                           st, sb, lengths, lambda, states, prev, labels, label_states);
+    hipLaunchKernelGGL((decode_wave_kernel<MODE, NT, FULL, COMPACT, CACHE>), dim3(unsigned(d.B)), dim3(kWave),
+                       size_t(kWave) * NT * sizeof(i32x2), d.stream, d.t, d.uni_base, d.asr, d.T, d.st, d.sb, d.lengths,
+                       d.lambda, d.states, d.prev, d.labels, d.label_states);
     return hipGetLastError();
+}
+
+template <int MODE, bool FULL>
+static hipError_t launch_wave(const Decode &d) {
+    if (d.t.dense_c)
+        return d.streams() ? launch_wave<MODE, FULL, true, kStream>(d) : launch_wave<MODE, FULL, true, kKeep>(d);
+    return d.streams() ? launch_wave<MODE, FULL, false, kStream>(d) : launch_wave<MODE, FULL, false, kKeep>(d);
 }
 
 // Wavefronts and tokens per lane, from a sweep over vocabularies and batches
@@ -504,44 +535,34 @@ static hipError_t launch_wave(const DevTrie &t, int uni_base, const float *asr, 
 //  - above: sixteen of 8 a lane: 290 / 671 / 720 at 64 / 500 / 1200 (42 frames)
 //    against 328 / 723 / 772 for eight of 16.
 template <int MODE>
-static hipError_t launch_mode(const DevTrie &t, const float *asr, int64_t B, int64_t T, int64_t sb, int64_t st,
-                              const int32_t *lengths, float lambda, int32_t *states, int32_t *prev, int32_t *labels,
-                              int32_t *label_states, hipStream_t stream) {
-    const int V = t.vocab_size;
-    // Dense row of the state entered by emitting w: row 1 + w when every token
-    // has a unigram (order-1 states are then numbered by token; <s>, if any,
-    // comes last), else (-1) read from the empty context's row.
-    const int n1 = (t.max_order > 2 ? t.first[2] : t.num_states) - 1;
-    const int uni = t.max_order > 1 && n1 == V + (t.final_w ? 1 : 0) ? 1 : -1;
-#define NGPU_DECODE(FN) return FN(t, uni, asr, B, T, sb, st, lengths, lambda, states, prev, labels, label_states, stream)
-    if (V <= 256) NGPU_DECODE((launch_group<MODE, 1, 4>));
-    if (V <= 512) NGPU_DECODE((launch_group<MODE, 1, 8>));
+static hipError_t launch_mode(const Decode &d) {
+    const int V = d.t.vocab_size;
+    if (V <= 256) return launch_group<MODE, 1, 4>(d);
+    if (V <= 512) return launch_group<MODE, 1, 8>(d);
     if (V <= 1024) {
-        if (B <= 1024) NGPU_DECODE((launch_group<MODE, 4, 4>));
-        if (V == 1024) NGPU_DECODE((launch_wave<MODE, true>));
-        NGPU_DECODE((launch_wave<MODE, false>));
+        if (d.B <= 1024) return launch_group<MODE, 4, 4>(d);
+        return V == 1024 ? launch_wave<MODE, true>(d) : launch_wave<MODE, false>(d);
     }
-    if (V <= 2048) {
-        if (B <= 768) NGPU_DECODE((launch_group<MODE, 8, 4>));
-        NGPU_DECODE((launch_group<MODE, 4, 8>));
-    }
-    if (V <= 4096) NGPU_DECODE((launch_group<MODE, 8, 8>));
-    NGPU_DECODE((launch_group<MODE, 16, 8>));
-#undef NGPU_DECODE
+    if (V <= 2048) return d.B <= 768 ? launch_group<MODE, 8, 4>(d) : launch_group<MODE, 4, 8>(d);
+    if (V <= 4096) return launch_group<MODE, 8, 8>(d);
+    return launch_group<MODE, 16, 8>(d);
 }
 
 hipError_t launch_fused_decode(const DevTrie &t, const float *asr, int64_t B, int64_t T, int64_t sb, int64_t st,
                                const int32_t *lengths, int mode, float lambda, int32_t *states, int32_t *prev,
                                int32_t *labels, int32_t *label_states, hipStream_t stream) {
-#define NGPU_MODE(M) \
-    return launch_mode<M>(t, asr, B, T, sb, st, lengths, lambda, states, prev, labels, label_states, stream)
+    // Dense row of the state entered by emitting w: row 1 + w when every token
+    // has a unigram (order-1 states are then numbered by token; <s>, if any,
+    // comes last), else (-1) read from the empty context's row.
+    const int n1 = (t.max_order > 2 ? t.first[2] : t.num_states) - 1;
+    const int uni = t.max_order > 1 && n1 == t.vocab_size + (t.final_w ? 1 : 0) ? 1 : -1;
+    const Decode d{t, uni, asr, B, T, sb, st, lengths, lambda, states, prev, labels, label_states, stream};
     switch (mode) {
-        case kPlain: NGPU_MODE(kPlain);
-        case kCtc: NGPU_MODE(kCtc);
-        case kAed: NGPU_MODE(kAed);
-        default: NGPU_MODE(kTransducer);
+        case kPlain: return launch_mode<kPlain>(d);
+        case kCtc: return launch_mode<kCtc>(d);
+        case kAed: return launch_mode<kAed>(d);
+        default: return launch_mode<kTransducer>(d);
     }
-#undef NGPU_MODE
 }
 
 }  // namespace ngpu

@@ -51,12 +51,13 @@ template <int NT>
 struct Words {
     int v[NT];
     // words lane, lane + 64, ... of the n >= 0 words at p; 0 past them
+    template <int CACHE = 0>
     __device__ __forceinline__ void load(const void *p, int n, int lane) {
         const __amdgpu_buffer_rsrc_t r = word_buffer(p, n);
         int at = lane * 4;
         asm volatile("" : "+v"(at));   // or the NT offsets are hoisted into registers of their own
 #pragma unroll
-        for (int i = 0; i < NT; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b32(r, at + kWave * i * 4, 0, 0);
+        for (int i = 0; i < NT; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b32(r, at + kWave * i * 4, 0, CACHE);
     }
     __device__ __forceinline__ float f(int i) const { return __int_as_float(v[i]); }
     // words past the first n become x
@@ -244,7 +245,10 @@ struct Group {
     __device__ __forceinline__ int token(int i) const { return t0 + kWave * i + lane; }
 
     // this wavefront's ASR scores of a row; tokens past V lose against everything
-    __device__ __forceinline__ void load_row(const float *row, Words<NT> &x) const { x.load(row + t0, own, lane); }
+    template <int CACHE = 0>
+    __device__ __forceinline__ void load_row(const float *row, Words<NT> &x) const {
+        x.template load<CACHE>(row + t0, own, lane);
+    }
     __device__ __forceinline__ void mask_row(Words<NT> &x) const {
         if (!FULL) x.pad(own, lane, -__builtin_inff());
     }

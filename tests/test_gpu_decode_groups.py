@@ -73,3 +73,15 @@ def test_decode_without_every_unigram(V, N, n1):
     m = tiny_model(V, N, seed=5, fill=0.02 if V > 50 else 0.5, n_unigrams=n1)
     asr = asr_logprobs((12, 70, V + 1), seed=V, blank_boost=2.0)
     check(m, asr, MODE_CTC, uniform_states(m, 12, seed=6))
+
+
+@pytest.mark.parametrize("V,B,T,mode", [(900, 1030, 75, MODE_TRANSDUCER), (2000, 700, 50, MODE_CTC)])
+def test_decode_streamed_rows(V, B, T, mode):
+    """ASR tensors above 256 MiB, whose rows are loaded non-temporally (the other
+    widths are decoded that way by the 20M 6-gram's tests)."""
+    m = generate_model(V, [V, 4 * V, 3 * V], 1.0, seed=V)
+    g = np.random.default_rng(V)
+    asr = g.standard_normal((B, T, V + 1), dtype=np.float32) * 3.0
+    asr[:, :, V] += 4.0
+    assert asr.nbytes > 256 << 20
+    check(m, asr, mode, uniform_states(m, B, seed=9))
