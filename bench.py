@@ -53,8 +53,8 @@ if ROOT not in sys.path:
 
 METRIC = "LM (state,token) scores/s + achieved HBM GB/s for batched advance; fused step/s"
 PEAK_HBM_GBPS = 8000.0
-KERNEL_SOURCES = ["paper_2505_22857_amd/csrc/advance.hip", "paper_2505_22857_amd/csrc/walk.h",
-                  "paper_2505_22857_amd/csrc/trie.h"]
+KERNEL_SOURCES = ["paper_2505_22857_amd/csrc/advance.hip", "paper_2505_22857_amd/csrc/group.h",
+                  "paper_2505_22857_amd/csrc/walk.h", "paper_2505_22857_amd/csrc/trie.h"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "advance_6gram20m_traffic.md")
 
 
