@@ -46,9 +46,8 @@ int hip_fail(hipError_t e, const char *what) {
     return fail(NGPU_E_HIP, "%s: %s", what, hipGetErrorString(e));
 }
 
-// Largest batch whose grid fits the 32-bit dispatch size in work-items: 64
-// per hypothesis (256 for the four-wavefront fused kernels, used up to 512
-// hypotheses only).
+// Largest batch whose grid fits the 32-bit dispatch size in work-items at one
+// wavefront per hypothesis; launches with more wavefronts split larger batches.
 constexpr int64_t kMaxBatch = NGPU_LM_MAX_BATCH;
 static_assert(kMaxBatch * 64 <= int64_t(UINT32_MAX), "grid must fit the dispatch size");
 

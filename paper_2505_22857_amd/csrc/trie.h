@@ -33,18 +33,18 @@
 //                        weight, folded through its backoff chain at build
 //                        time (Section 2.3, AED)
 //   dense_c    float [R * V]  the dense rows again in 4 bytes per token, for
-//   dense_base int32 [R]      the whole-decode kernel that holds rows in
-//            registers, which needs a token's next state only for the frame's
-//            winner: dense_c is the weight's magnitude, its sign bit set where
-//            the entry backed off to the empty context (DENSE_BACKOFF), so
-//            weight = dense_c with the sign bit set.  A backed-off token v (and
-//            every token of row 0) leads to the unigram state first[1] + v; an
-//            own bigram of row u leads to dense_base[u] + the number of own
-//            bigrams of row u below it when compact_rank is set (orders >= 3:
-//            bigrams are states, numbered in the row's token order), else to
-//            first[1] + v.  Present (off_dense_c != 0) only when V <= 1024,
-//            every dense weight has its sign bit set and these rules give
-//            dense_to exactly for every entry, which the builder checks.
+//   dense_base int32 [R]      the whole decode of large batches, which needs a
+//            token's next state only for the frame's winner: dense_c is the
+//            weight's magnitude, its sign bit set where the entry backed off to
+//            the empty context (DENSE_BACKOFF), so weight = dense_c with the
+//            sign bit set.  A backed-off token v (and every token of row 0)
+//            leads to the unigram state first[1] + v; an own bigram of row u
+//            leads to dense_base[u] + the number of own bigrams of row u below
+//            it when compact_rank is set (orders >= 3: bigrams are states,
+//            numbered in the row's token order), else to first[1] + v.  Present
+//            (off_dense_c != 0) only when V <= 1024, every dense weight has its
+//            sign bit set and these rules give dense_to exactly for every entry,
+//            which the builder checks.
 #pragma once
 
 #include <cstddef>
