@@ -268,10 +268,10 @@ __device__ __forceinline__ int pick(const Words<NT> &x, int j, int l) {
 // plain argmax needs the row's maximum only (three-input maxima): blank is
 // above it or not, and a repeat is the previous label holding it; the winner's
 // token is searched where the wave's maximum is found.  4096 utterances x 200
-// frames, V = 1024: 782 us (820 in the kernel before, 8-byte slots and one frame's
-// chain in line); without any LM work the stream of ASR rows (3.36 GB) alone takes
-// 670.  V = 700, 100 frames: 329 us (673 before).
-template <int MODE, int NT, bool FULL, bool COMPACT, int CACHE>
+// frames, V = 1024: 811 us (820 in the kernel before, 8-byte slots and one frame's
+// chain in line), 883 (893) on rows just written; without any LM work the stream
+// of ASR rows (3.36 GB) alone takes 670.  V = 700, 100 frames: 329 us (673 before).
+template <int MODE, int NT, bool FULL, bool COMPACT>
 __global__ __launch_bounds__(kWave, (COMPACT ? 4 : 1)) void decode_wave_kernel(
     DevTrie t, int uni_base, const float *__restrict__ asr, int64_t T, int64_t stride_t, int64_t stride_b,
     const int32_t *__restrict__ lengths, float lambda, int32_t *__restrict__ states, int32_t *__restrict__ prev,
@@ -305,7 +305,7 @@ __global__ __launch_bounds__(kWave, (COMPACT ? 4 : 1)) void decode_wave_kernel(
     Words<NT> bufa, bufb;
     float va = 0.0f, vb = 0.0f;
     auto load_row = [&](const float *row, Words<NT> &x, float &v) {
-        x.template load<CACHE>(row, V, lane);
+        x.load(row, V, lane);
         if (MODE != kPlain) v = row[V + zero];
     };
     int4 rec;
@@ -464,10 +464,12 @@ struct Decode {
     int32_t *states, *prev, *labels, *label_states;
     hipStream_t stream;
     // The ASR rows outgrow the Infinity Cache: stream them.  us a launch, kept
-    // against streamed: 1.05 GB (256 x 1000, 20M 6-gram) 1827 / 1712, 3.4 GB (4096 x
-    // 200) 811 / 782, 615 MB (1000 x 150, V = 1024) 306 / 300; 246 MB (300 x 200)
-    // 327 / 327; 216 MB (600 x 60, V = 1500) 137 / 144, 48 MB (40 x 200) 295 / 325:
-    // a smaller tensor may still be cached from its writer.
+    // against streamed, repeated and (in brackets) first after the tensor was
+    // written: 1.05 GB (256 x 1000, 20M 6-gram) 1824 / 1702 [1863 / 1810], 615 MB
+    // (1000 x 150, V = 1024) 361 / 345 [403 / 383], 1.08 GB (3000 x 60, V = 1500) 460 /
+    // 456 [494 / 472]; 246 MB (300 x 200) 327 / 327, 216 MB (600 x 60, V = 1500) 137 /
+    // 144, 48 MB (40 x 200) 295 / 325: a smaller tensor may still be cached from its
+    // writer.
     bool streams() const {
         const double row = 4.0 * (t.vocab_size + 1);
         return double(B) * double(T) * row > 256.0 * (1 << 20);
@@ -491,7 +493,10 @@ static hipError_t launch_group(const Decode &d) {
 }
 
 // Rows of up to 512 tokens are always kept: streamed, V = 128 took 143 against
-// 136 us at 1500 utterances, 178 against 165 at 4000 (two rows share a line).
+// 136 us at 1500 utterances, 178 against 165 at 4000 (two rows share a line).  So
+// are those of decode_wave_kernel: streamed, 4096 x 200 took 800 instead of 820 us
+// repeated, but 903 instead of 883 on a tensor just written, which a decode
+// after the acoustic model finds.
 template <int MODE, int W, int NT>
 static hipError_t launch_group(const Decode &d) {
     const bool full = d.t.vocab_size == W * kWave * NT;
@@ -502,10 +507,10 @@ static hipError_t launch_group(const Decode &d) {
     return full ? launch_group<MODE, W, NT, true, kKeep>(d) : launch_group<MODE, W, NT, false, kKeep>(d);
 }
 
-template <int MODE, bool FULL, bool COMPACT, int CACHE>
+template <int MODE, bool FULL, bool COMPACT>
 static hipError_t launch_wave(const Decode &d) {
     constexpr int NT = 16;
-    hipLaunchKernelGGL((decode_wave_kernel<MODE, NT, FULL, COMPACT, CACHE>), dim3(unsigned(d.B)), dim3(kWave),
+    hipLaunchKernelGGL((decode_wave_kernel<MODE, NT, FULL, COMPACT>), dim3(unsigned(d.B)), dim3(kWave),
                        size_t(kWave) * NT * sizeof(i32x2), d.stream, d.t, d.uni_base, d.asr, d.T, d.st, d.sb, d.lengths,
                        d.lambda, d.states, d.prev, d.labels, d.label_states);
     return hipGetLastError();
@@ -513,9 +518,7 @@ static hipError_t launch_wave(const Decode &d) {
 
 template <int MODE, bool FULL>
 static hipError_t launch_wave(const Decode &d) {
-    if (d.t.dense_c)
-        return d.streams() ? launch_wave<MODE, FULL, true, kStream>(d) : launch_wave<MODE, FULL, true, kKeep>(d);
-    return d.streams() ? launch_wave<MODE, FULL, false, kStream>(d) : launch_wave<MODE, FULL, false, kKeep>(d);
+    return d.t.dense_c ? launch_wave<MODE, FULL, true>(d) : launch_wave<MODE, FULL, false>(d);
 }
 
 // Wavefronts and tokens per lane, from a sweep over vocabularies and batches
