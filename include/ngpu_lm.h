@@ -202,7 +202,7 @@ enum ngpu_fusion_mode {
  *   LM score; <eos> leaves the state unchanged, a token advances it.
  * Ties go to the lowest index (-0 equals +0).  ASR scores may be -inf: a
  * candidate set entirely at -inf yields its first candidate, as a strict '>'
- * scan from index 0 does; NaN is not supported.  In/out: d_states[B] (int32), d_prev[B] (CTC
+ * scan from index 0 does; a (quiet) NaN counts as -inf.  In/out: d_states[B] (int32), d_prev[B] (CTC
  * only; may be NULL otherwise).  Out: d_tokens[B] (int32 label, V = blank).
  * Out-of-range states give label -1, leave the state unchanged and are counted
  * for ngpu_lm_check_states.  Asynchronous on hip_stream. */

@@ -119,7 +119,7 @@ __global__ __launch_bounds__(W * kWave) void decode_kernel(DevTrie t, int uni_ba
             bool lm = true;
             if (kRaw) {
                 label = raw_tok;                                      // every token at -inf: the lowest, 0
-                if (float_key(rowV) > raw_key) label = V;             // blank only when strictly larger (highest index)
+                if (float_key(or_lowest(rowV)) > raw_key) label = V;  // blank only when strictly larger (highest index)
                 lm = !(label == V || (MODE == kCtc && label == pv));  // blank or repeat: no LM, no move
             }
             unsigned fkey = 0;
@@ -177,7 +177,7 @@ __global__ __launch_bounds__(W * kWave) void decode_kernel(DevTrie t, int uni_ba
             bool moved = lm;
             if (MODE == kAed) {   // <eos> strictly above every token: the sentence ends, the state stays
                 const float fw = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(fin)));
-                if (float_key(__builtin_fmaf(lambda, fw, rowV)) > fkey) {
+                if (float_key(or_lowest(__builtin_fmaf(lambda, fw, rowV))) > fkey) {
                     label = V;
                     moved = false;
                 }
@@ -243,11 +243,13 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
     asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
     return r;
 }
+// The lane's largest word, -inf where all are NaN.
 template <int NT>
 __device__ __forceinline__ float lane_max(const Words<NT> &x) {
+    static_assert(NT % 2 == 0, "the last maximum takes -inf beside the last word");
     float r = max3(x.f(0), x.f(1), x.f(2));
 #pragma unroll
-    for (int i = 3; i < NT; i += 2) r = max3(r, x.f(i), x.f(i + 1 < NT ? i + 1 : i));
+    for (int i = 3; i < NT; i += 2) r = max3(r, x.f(i), i + 1 < NT ? x.f(i + 1) : -__builtin_inff());
     return r;
 }
 // Value of token 64 j + l (both uniform) of the words.
@@ -341,9 +343,14 @@ __global__ __launch_bounds__(kWave, (COMPACT ? 4 : 1)) void decode_wave_kernel(
         if (kRaw) {
             const unsigned mk = wave_max_u32(float_key(lane_max(cur)));
             const float rowV = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(cur_v)));
-            if (float_key(rowV) > mk) {   // blank only when strictly larger
+            if (float_key(or_lowest(rowV)) > mk) {   // blank only when strictly larger
                 label = V;
                 lm = false;
+            } else if (MODE == kCtc && mk == kInfKey) {   // no token above -inf: the first one, a repeat of label 0
+                if (pv == 0) {
+                    label = 0;
+                    lm = false;
+                }
             } else if (MODE == kCtc && pv >= 0 && pv < V) {
                 const float at = __int_as_float(pick<0, NT>(cur, pv >> 6, pv & (kWave - 1)));
                 if (float_key(at) == mk) {   // the previous label holds the maximum: a repeat unless a lower token does too
@@ -399,10 +406,12 @@ __global__ __launch_bounds__(kWave, (COMPACT ? 4 : 1)) void decode_wave_kernel(
             } else {
                 int w = 0, rank = 0, to = 0;
                 bool own = false;
-                // every candidate at -inf: the first one (the excluded label is NaN, not -inf)
 #pragma unroll
                 for (int i = 0; i < NT; ++i) {
-                    const unsigned long long m = __ballot(cur.f(i) == best);
+                    unsigned long long m = __ballot(cur.f(i) == best);
+                    // no candidate above -inf (words past V are at -inf too): the
+                    // first one.  Else the best is a token's: w < V.
+                    if (i == 0 && mk == kInfKey) m = MODE == kCtc && pv == 0 ? 2 : 1;
                     const unsigned long long o = COMPACT ? __ballot(dw.v[i] >= 0) : 0;
                     if (m) {
                         const int l = int(__builtin_ctzll(m));

@@ -74,7 +74,7 @@ __global__ __launch_bounds__(W * kWave) void step_kernel(DevTrie t, const float 
             key = unsigned(__builtin_amdgcn_readlane(k, e));
             label = __builtin_amdgcn_readlane(tk, e);
         }
-        if (float_key(rowV) > key) label = V;                 // blank only when strictly larger (highest index)
+        if (float_key(or_lowest(rowV)) > key) label = V;      // blank only when strictly larger (highest index)
         lm = !(label == V || (MODE == kCtc && label == pv));  // blank or repeat: no LM, no move
     }
     if (lm) {
@@ -118,7 +118,7 @@ __global__ __launch_bounds__(W * kWave) void step_kernel(DevTrie t, const float 
         bool eos = false;
         if (MODE == kAed) {   // <eos> strictly above every token: the sentence ends, the state stays
             const float fw = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(fin)));
-            eos = float_key(__builtin_fmaf(lambda, fw, rowV)) > key;
+            eos = float_key(or_lowest(__builtin_fmaf(lambda, fw, rowV))) > key;
         }
         if (eos) {
             label = V;

@@ -74,6 +74,10 @@ __device__ __forceinline__ unsigned float_key(float x) {
     return unsigned(u ^ ((u >> 31) | int(0x80000000u)));
 }
 constexpr unsigned kInfKey = 0x007fffffu;   // float_key(-inf)
+// x, or -inf where x is NaN: a NaN score loses as under a strict '>' scan from
+// -inf.  (Its key would lie above +inf's or, with the sign bit set, below
+// -inf's, where a lane that holds no token would win against it.)
+__device__ __forceinline__ float or_lowest(float x) { return __builtin_fmaxf(x, -__builtin_inff()); }
 
 // The chain tables over the lanes: lane k holds the first state of order k
 // (k >= 1, else a bound no state reaches), the address that record(s) = base +
@@ -330,8 +334,9 @@ struct Group {
         }
     }
     // The lane's largest value and its place 64 i; ties stay with the lowest token.
+    // Never NaN, and above -inf only for a token below V.
     __device__ __forceinline__ void lane_best(const float (&x)[NT], float &bx, int &bi) const {
-        bx = x[0];
+        bx = or_lowest(x[0]);
         bi = 0;
 #pragma unroll
         for (int i = 1; i < NT; ++i) {
