@@ -220,7 +220,7 @@ int ngpu_lm_fused_greedy_step(const ngpu_lm *lm, const float *d_asr, int64_t B, 
  * the fused score, ties to the lower token index: d_tokens (int32), d_scores
  * (fp32 fused scores), d_next (int32 state after that token); when fewer
  * than k tokens score above -inf, the rest follow in index order (as a strict
- * '>' selection gives).  States are read only.
+ * '>' selection gives; a NaN score counts as -inf).  States are read only.
  * 1 <= k <= min(V, NGPU_LM_MAX_TOPK); cost per hypothesis: one pass over the V
  * tokens, then a selection whose cost hardly grows with k (a lower bound of the
  * k-th largest value, a short list of the tokens that reach it, and each

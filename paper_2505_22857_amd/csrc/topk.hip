@@ -80,7 +80,8 @@ __global__ __launch_bounds__(W * kWave) void topk_kernel(DevTrie t, const float 
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
         x[i] = __builtin_fmaf(lambda, x[i], row.f(i));
-        key[i] = FULL || kWave * i + lane < g.own ? float_key(x[i]) : 0u;   // past V: below every token's key
+        // a token's key lies from -inf's (also a NaN's) to +inf's, below ~0; past V: below every token's
+        key[i] = FULL || kWave * i + lane < g.own ? float_key(or_lowest(x[i])) : 0u;
         m = max(m, key[i]);
     }
 

@@ -96,3 +96,27 @@ def test_greedy(V, B, mode, dense4):
         assert np.array_equal(got.cpu().numpy(), want[:, t]), t
         assert np.array_equal(st.cpu().numpy(), after[:, t]), t
     assert lm.check_states() == 0
+
+
+@pytest.mark.parametrize("V,B,k", [(63, 64, 63), (200, 64, 100), (400, 64, 200), (700, 64, 16), (1024, 64, 256),
+                                   (1500, 64, 1), (2048, 64, 40), (3000, 64, 256), (4096, 200, 16), (5000, 64, 32),
+                                   (8192, 64, 256)])
+def test_topk(V, B, k):
+    """Also more NaNs of one bit pattern than the selection's list holds, and none
+    of the k places left unwritten."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU visible")
+    m = generate_model(V, [V, 3 * V, 2 * V], 1.0, seed=V)
+    lm, o = ng.NgpuLM.from_model(m).upload("cuda:0"), Oracle.from_model(m)
+    asr = spoil(asr_logprobs((B, 1, V), seed=V, blank_boost=0.0), V, V + 1)[:, 0].copy()
+    states = uniform_states(m, B, seed=B)
+    for lam in (0.0, 0.5):
+        tok = torch.full((B, k), -7, dtype=torch.int32, device="cuda")
+        print(f"[case] top-k V={V} B={B} k={k} lambda={lam}", flush=True)
+        _, sc, nx = lm.fused_topk(torch.from_numpy(asr).cuda(), lam, k, torch.from_numpy(states).cuda(), tok)
+        assert lm.check_states() == 0
+        wt, ws, wn = o.fused_topk(without_nan(asr), lam, k, states)
+        assert np.array_equal(tok.cpu().numpy(), wt)
+        assert np.array_equal(nx.cpu().numpy(), wn)
+        nan = np.isnan(np.take_along_axis(asr, wt, 1))   # their scores come out as they are
+        assert np.array_equal(sc.cpu().numpy(), np.where(nan, np.float32(np.nan), ws), equal_nan=True)
