@@ -4,7 +4,9 @@
 // Each function answers the ordinary call (plain contiguous device tensors,
 // the current stream) and returns None for anything else, which the Python
 // method then handles, and reports, by itself; a failing C call returns its
-// code.
+// code.  Everything that can fail otherwise, the results' Python objects among
+// it, comes before the C call: after it the step has been enqueued, and None
+// would make the Python method enqueue it a second time.
 //
 // An enqueued call cost the host 4.4 us (advance) to 9.9 us (top-k, three
 // outputs allocated), more than the kernels of small batches take, and 2.4 us
@@ -26,7 +28,23 @@ decltype(&ngpu_lm_advance) g_advance;
 decltype(&ngpu_lm_fused_greedy_step) g_step;
 decltype(&ngpu_lm_fused_topk) g_topk;
 
-PyObject *none() { Py_RETURN_NONE; }
+PyObject *none() {
+    PyErr_Clear();   // the Python method meets the error again, or does not
+    Py_RETURN_NONE;
+}
+
+struct Ref {   // an owned reference
+    PyObject *p = nullptr;
+    Ref() = default;
+    explicit Ref(PyObject *o) : p(o) {}
+    Ref(const Ref &) = delete;
+    ~Ref() { Py_XDECREF(p); }
+    PyObject *release() {
+        PyObject *o = p;
+        p = nullptr;
+        return o;
+    }
+};
 
 const at::Tensor *tensor_of(PyObject *o, at::ScalarType type) {
     if (!THPVariable_CheckExact(o)) return nullptr;
@@ -40,23 +58,20 @@ const at::Tensor *dense(PyObject *o, at::ScalarType type) {
 
 // An output: the caller's contiguous tensor of at least n entries, or a new one.
 struct Output {
-    PyObject *given = nullptr;
+    Ref object;
     at::Tensor t;
     bool set(PyObject *o, at::ScalarType type, int64_t n, at::IntArrayRef shape, const at::Tensor &like) {
         if (o == Py_None) {
             t = at::empty(shape, like.options().dtype(type));
-            return t.is_contiguous();
+            object.p = THPVariable_Wrap(t);
+            return object.p && t.is_contiguous();
         }
         const at::Tensor *x = dense(o, type);
         if (!x || x->numel() < n) return false;
-        given = o;
+        Py_INCREF(o);
+        object.p = o;
         t = *x;
         return true;
-    }
-    PyObject *object() {
-        if (!given) return THPVariable_Wrap(t);
-        Py_INCREF(given);
-        return given;
     }
 };
 
@@ -96,16 +111,13 @@ PyObject *advance(PyObject *, PyObject *const *a, Py_ssize_t n) try {
     const auto *st = static_cast<const int32_t *>(states->data_ptr());
     auto *sc = static_cast<float *>(scores.t.data_ptr());
     auto *nx = static_cast<int32_t *>(next.t.data_ptr());
+    Ref result(PyTuple_Pack(2, scores.object.p, next.object.p));
+    if (!result.p) return none();
     void *stream = current_stream();
     const int rc = without_gil([&] { return g_advance(reinterpret_cast<const ngpu_lm *>(h), st, B, sc, nx, stream); });
-    if (rc != NGPU_OK) return PyLong_FromLong(rc);
-    PyObject *x = scores.object(), *y = next.object();
-    PyObject *r = x && y ? PyTuple_Pack(2, x, y) : nullptr;
-    Py_XDECREF(x);
-    Py_XDECREF(y);
-    return r;
+    return rc != NGPU_OK ? PyLong_FromLong(rc) : result.release();
 } catch (const std::exception &) {
-    return none();   // nothing was enqueued: the C call throws nothing
+    return none();   // nothing was enqueued: the C call, and what follows it, throws nothing
 }
 
 // step(handle, V, asr, lam, states, prev or None, mode, tokens or None)
@@ -132,7 +144,7 @@ PyObject *step(PyObject *, PyObject *const *a, Py_ssize_t n) try {
         return g_step(reinterpret_cast<const ngpu_lm *>(h), row, B, ld, static_cast<int32_t>(mode), lam, st, pv, tk,
                       stream);
     });
-    return rc != NGPU_OK ? PyLong_FromLong(rc) : tokens.object();
+    return rc != NGPU_OK ? PyLong_FromLong(rc) : tokens.object.release();
 } catch (const std::exception &) {
     return none();
 }
@@ -158,18 +170,14 @@ PyObject *topk(PyObject *, PyObject *const *a, Py_ssize_t n) try {
     auto *sc = static_cast<float *>(scores.t.data_ptr());
     auto *nx = static_cast<int32_t *>(next.t.data_ptr());
     const int64_t ld = asr->stride(0);
+    Ref result(PyTuple_Pack(3, tokens.object.p, scores.object.p, next.object.p));
+    if (!result.p) return none();
     void *stream = current_stream();
     const int rc = without_gil([&] {
         return g_topk(reinterpret_cast<const ngpu_lm *>(h), row, B, ld, lam, static_cast<int32_t>(k), st, tk, sc, nx,
                       stream);
     });
-    if (rc != NGPU_OK) return PyLong_FromLong(rc);
-    PyObject *x = tokens.object(), *y = scores.object(), *z = next.object();
-    PyObject *r = x && y && z ? PyTuple_Pack(3, x, y, z) : nullptr;
-    Py_XDECREF(x);
-    Py_XDECREF(y);
-    Py_XDECREF(z);
-    return r;
+    return rc != NGPU_OK ? PyLong_FromLong(rc) : result.release();
 } catch (const std::exception &) {
     return none();
 }

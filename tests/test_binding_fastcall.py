@@ -97,3 +97,27 @@ def test_other_streams_and_refusals(lm):
         lm.fused_greedy_step(asr, float("nan"), states)
     with pytest.raises(ng.NgpuError):
         lm.fused_greedy_step(asr, 0.5, states, mode=ng.NGPU_FUSION_AED)   # no </s> in the model
+
+
+@pytest.mark.gpu
+def test_a_failed_allocation_leaves_the_states_alone(lm):
+    """The step's result object is made before the step is enqueued: where that
+    fails, the native path declines and nothing has moved; the call is then
+    made, once, by the Python path."""
+    hooks = pytest.importorskip("_testcapi")
+    asr = torch.randn((5, 10), generator=torch.Generator(device="cuda").manual_seed(3), device="cuda")
+    start = torch.zeros(5, dtype=torch.int32, device="cuda")
+    want_st = start.clone()
+    want = lm.fused_greedy_step(asr, 0.5, want_st)
+    assert (want_st != start).any()
+    st = start.clone()
+    torch.cuda.synchronize()
+    step, args = lm._fast.step, (lm._h.value, lm.vocab_size, asr, 0.5, st, None, 0, None)
+    try:
+        hooks.set_nomemory(0, 1)   # the first allocation fails, no other
+        r = step(*args)
+    finally:
+        hooks.remove_mem_hooks()
+    torch.cuda.synchronize()
+    assert r is None and torch.equal(st, start)
+    assert torch.equal(lm.fused_greedy_step(asr, 0.5, st), want) and torch.equal(st, want_st)
