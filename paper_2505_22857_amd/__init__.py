@@ -5,7 +5,8 @@ Every step of a query runs in the library's HIP kernels; this module only
 marshals arguments, for the per-frame calls through the small native module
 ``_fastcall.so`` (``csrc/fastcall.cpp``).  PyTorch supplies device memory and the current HIP
 stream.  The library must be built first (``__graft_entry__.build()`` or
-``python -m paper_2505_22857_amd.build``); without it every call raises.
+``python -m paper_2505_22857_amd.build``); without it every call raises.  Without a
+``_fastcall.so`` for the installed torch, those calls go through ctypes as all others do.
 """
 
 from __future__ import annotations
@@ -112,24 +113,39 @@ _fast = None
 
 
 def _load_fast():
-    """The native per-call module, bound to the loaded library; raises if it has not been built."""
+    """The native per-call module, bound to the loaded library; raises ImportError where it has not
+    been built, or was built against another torch (whose C++ classes may be laid out differently)."""
     global _fast
     if _fast is None:
         import importlib.machinery
         import importlib.util
 
-        import torch  # noqa: F401  (the module links against torch's libraries)
+        import torch
         if not os.path.exists(FAST_PATH):
-            raise RuntimeError(f"{FAST_PATH} is missing: build it with __graft_entry__.build()")
+            raise ImportError(f"{FAST_PATH} is missing")
         name = __name__ + "._fastcall"
         loader = importlib.machinery.ExtensionFileLoader(name, FAST_PATH)
         mod = importlib.util.module_from_spec(importlib.util.spec_from_loader(name, loader))
         loader.exec_module(mod)
+        built = mod.torch_version() if hasattr(mod, "torch_version") else "of an earlier build"
+        if built != torch.__version__:
+            raise ImportError(f"{FAST_PATH} was built against torch {built}, not {torch.__version__}")
         lib = load_library()
         mod.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in
                    (lib.ngpu_lm_advance, lib.ngpu_lm_fused_greedy_step, lib.ngpu_lm_fused_topk)))
         _fast = mod
     return _fast
+
+
+def _fast_or_none():
+    """The native per-call module, or None, with a warning, where it cannot be used: every call
+    works without it and costs the host about twice as long."""
+    try:
+        return _load_fast()
+    except ImportError as e:
+        import warnings
+        warnings.warn(f"calls go through ctypes: {e} (__graft_entry__.build() makes it)", RuntimeWarning, stacklevel=3)
+        return None
 
 
 def _check(rc: int):
@@ -256,7 +272,7 @@ class NgpuLM:
     def upload(self, device="cuda", stream=None):
         """Allocate the device image with torch and copy the trie into it."""
         import torch
-        self._fast = _load_fast()
+        self._fast = _fast_or_none()
         buf = torch.empty(self.device_bytes + 256, dtype=torch.uint8, device=device)
         off = (-buf.data_ptr()) % 256
         view = buf[off:off + self.device_bytes]

@@ -45,6 +45,7 @@ def build_fastcall(out: str = FAST_PATH, verbose: bool = False) -> str:
     from torch.utils.cpp_extension import include_paths, library_paths
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f'-DNGPU_TORCH_VERSION="{torch.__version__}"',
            *[x for p in include_paths("cuda") for x in ("-isystem", p)],
            "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"),
            os.path.join(CSRC, "fastcall.cpp"), *[f"-L{p}" for p in library_paths("cuda") if os.path.isdir(p)],

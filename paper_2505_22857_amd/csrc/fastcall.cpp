@@ -195,12 +195,16 @@ PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n) {
     return none();
 }
 
+// The torch.__version__ of the headers this was compiled with.
+PyObject *torch_version(PyObject *, PyObject *const *, Py_ssize_t) { return PyUnicode_FromString(NGPU_TORCH_VERSION); }
+
 template <PyObject *(*F)(PyObject *, PyObject *const *, Py_ssize_t)>
 PyMethodDef method(const char *name) {
     return {name, reinterpret_cast<PyCFunction>(reinterpret_cast<void *>(F)), METH_FASTCALL, nullptr};
 }
 PyMethodDef g_methods[] = {method<advance>("advance"), method<step>("step"), method<topk>("topk"),
-                           method<bind>("bind"), {nullptr, nullptr, 0, nullptr}};
+                           method<bind>("bind"), method<torch_version>("torch_version"),
+                           {nullptr, nullptr, 0, nullptr}};
 PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_fastcall", nullptr, -1, g_methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

@@ -23,6 +23,24 @@ def test_declines_what_is_not_a_plain_device_tensor():
     assert fast.topk(0, 9, asr, 0.5, 4, st, None, None, None) is None
 
 
+@pytest.fixture(params=["missing", "no library", "another torch"])
+def unusable(request, monkeypatch, tmp_path):
+    """No native module, a file that does not load, one built against another torch."""
+    monkeypatch.setattr(ng, "_fast", None)
+    if request.param == "another torch":
+        monkeypatch.setattr(torch, "__version__", "0.1")
+    else:
+        monkeypatch.setattr(ng, "FAST_PATH", str(tmp_path / "_fastcall.so"))
+        if request.param == "no library":
+            (tmp_path / "_fastcall.so").write_bytes(b"not a library")
+
+
+def test_unusable_module_is_left_out(unusable):
+    with pytest.warns(RuntimeWarning, match="ctypes"):
+        assert ng._fast_or_none() is None
+    assert ng._fast is None
+
+
 @pytest.fixture(scope="module")
 def lm():
     if not torch.cuda.is_available():
@@ -64,6 +82,15 @@ def test_same_results_as_the_python_path(lm, B):
     assert lm.fused_greedy_step(wide[:, :10], 0.5, st, pv, mode=ng.NGPU_FUSION_CTC, tokens=tok) is tok
     sc = torch.empty((B, 9), device="cuda")
     assert lm.advance(states, sc)[0] is sc
+
+
+@pytest.mark.gpu
+def test_upload_without_the_module(lm, unusable):
+    with pytest.warns(RuntimeWarning, match="ctypes"):
+        plain = ng.NgpuLM.from_model(tiny_model(9, 3, seed=21)).upload("cuda:0")
+    states = torch.arange(4, dtype=torch.int32, device="cuda")
+    got, want = plain.advance(states), lm.advance(states)
+    assert plain._fast is None and torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
 
 
 @pytest.mark.gpu
