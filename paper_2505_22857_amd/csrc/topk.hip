@@ -23,6 +23,7 @@
 // at V = 5000, k = 32, against 7.5 and 10.1 here.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -45,9 +46,10 @@ __global__ __launch_bounds__(W * kWave) void topk_kernel(DevTrie t, const float 
     const int64_t b = blockIdx.x;
     const int V = t.vocab_size;
     Meet *meet = reinterpret_cast<Meet *>(lds4);
+    const Group<W, NT, FULL> g(V, reinterpret_cast<i32x2 *>(meet + 1));
+    // the list takes the slots' place: every wavefront has read its slots before the barrier of the first exchange
     unsigned long long *lkey = reinterpret_cast<unsigned long long *>(meet + 1);   // kList: key, ~token
     i32x2 *lval = reinterpret_cast<i32x2 *>(lkey + kList);                         // kList: score, next state
-    const Group<W, NT, FULL> g(V, lval + kList);
     const int wave = g.wave, lane = g.lane, tid = threadIdx.x;
     int32_t *otok = tokens + b * k;
     float *osc = scores + b * k;
@@ -218,7 +220,7 @@ template <int W, int NT>
 static hipError_t launch(const DevTrie &t, const float *asr, int64_t B, int64_t ld, float lambda, int k,
                          const int32_t *states, int32_t *tokens, float *scores, int32_t *next, hipStream_t stream) {
     constexpr int64_t kMost = int64_t(UINT32_MAX) / (W * kWave);
-    const size_t lds = sizeof(Meet) + size_t(list_size<W>()) * 16 + size_t(W) * kWave * NT * sizeof(i32x2);
+    const size_t lds = sizeof(Meet) + std::max(size_t(list_size<W>()) * 16, size_t(W) * kWave * NT * sizeof(i32x2));
     const dim3 block(W * kWave);
     for (int64_t b0 = 0; b0 < B; b0 += kMost) {
         const dim3 grid{unsigned(B - b0 < kMost ? B - b0 : kMost)};
@@ -233,15 +235,26 @@ static hipError_t launch(const DevTrie &t, const float *asr, int64_t B, int64_t 
     return hipSuccess;
 }
 
-// Wavefronts and tokens per lane, from sweeps over vocabularies, batches and k
-// (us a call; in brackets the choice next to it):
+// Wavefronts and tokens per lane, from sweeps over vocabularies, batches (8 to
+// 12000) and k (1 to 200); us a call, in brackets the choice next to it.  Few
+// hypotheses get more wavefronts each, which rank a long list sooner; many get
+// fewer, since every wavefront repeats the walk, the exchanges and the counts.
 //  - V <= 256: one wavefront, 6.1 at V = 128, 4000 hypotheses, k = 16 [two: 9.2];
-//    two for large k and few hypotheses, where ranking the list takes longest:
-//    6.5 at 300, k = 100 [8.0].
-//  - V <= 512 (V = 400): one up to k = 32, 6.9 at 4000, k = 16 [two: 9.4]; two up
-//    to 96, 6.3 at 300, k = 64 [one: 7.4]; four above, 10.1 at 300, k = 200 [two:
-//    13.3].
-//  - V <= 1024: four of 4 a lane, 7.4 at 300, k = 64 [two of 8: 8.0].
+//    two for large k and few hypotheses, 6.5 at 300, k = 100 [8.0].
+//  - V <= 512 (V = 400): one up to k = 32, 6.9 at 4000, k = 16 [two: 9.4]; up to
+//    1024 hypotheses two up to k = 96, 6.3 at 300, k = 64 [one: 7.4], four above,
+//    10.3 at 300, k = 200 [two: 11.1]; beyond (1280 for large k) one, 10.0 / 24.6 at
+//    4096, k = 64 / 200 [two: 12.0 / 26.2, four: 32.6 for 200], up to the 8192 where
+//    two win.
+//  - V <= 768: four of 4 a lane up to 1024 hypotheses (1536 for large k: 14.5 at 1025,
+//    k = 200, one of 12 15.6); beyond one of 12, 8.4 / 10.5 / 13.2 / 26 at V = 700, 4096,
+//    k = 1 / 16 / 64 / 200 [four: 12.6 / 16.4 / 20.4 / 34].
+//  - V <= 1024: four of 4, 7.4 at 300, k = 64 [two of 8: 8.0], also for large k;
+//    beyond 1024 hypotheses two of 8 up to k = 96, 9.5 / 17.1 at 2048 / 4096, k = 64
+//    [four: 12.4 / 20.5].
+//  - V <= 1536: four of 8 up to 768 hypotheses, also for large k; beyond two of 10
+//    or 12 up to k = 96, 5.9 / 12.5 at V = 1100, 1024 / 4096, k = 1 [four: 7.3 / 16.8]
+//    and 8.9 / 19.4 at k = 64, 1024 / 4096 [10.3 / 25].
 //  - V <= 2048: four of 8, 6.9 / 19.1 at 300, k = 32 / 4000, k = 16 [eight of 4:
 //    7.8 / 30.5].
 //  - V <= 4096 (V = 4000): eight of 8 for few hypotheses, 6.0 at 8 [four of 16: 6.7],
@@ -258,11 +271,19 @@ hipError_t launch_fused_topk(const DevTrie &t, const float *asr, int64_t B, int6
         NGPU_TOPK(1, 4);
     }
     if (V <= 512) {
-        if (k > 96) NGPU_TOPK(4, 2);
-        if (k > 32) NGPU_TOPK(2, 4);
+        if (k > 96 && B <= 1280) NGPU_TOPK(4, 2);
+        if (k > 32 && (B <= 1024 || (k > 96 && B > 8192))) NGPU_TOPK(2, 4);
         NGPU_TOPK(1, 8);
     }
-    if (V <= 1024) NGPU_TOPK(4, 4);
+    if (V <= 768 && B > (k > 96 ? 1536 : 1024)) NGPU_TOPK(1, 12);
+    if (V <= 1024) {
+        if (k <= 96 && B > 1024) NGPU_TOPK(2, 8);
+        NGPU_TOPK(4, 4);
+    }
+    if (V <= 1536 && k <= 96 && B > 768) {
+        if (V <= 1280) NGPU_TOPK(2, 10);
+        NGPU_TOPK(2, 12);
+    }
     if (V <= 2048) NGPU_TOPK(4, 8);
     if (V <= 4096) {
         if (B <= 128) NGPU_TOPK(8, 8);

@@ -42,23 +42,27 @@ def check_topk(V, B, k, asr, lam=0.5):
 @pytest.mark.parametrize("V,B,k", [
     (1, 3, 1), (5, 3, 5), (63, 3, 17), (64, 2, 64), (65, 2, 65), (200, 5, 200), (256, 1030, 256), (257, 4, 33),
     (400, 3, 97), (512, 3, 256), (513, 4, 5), (1024, 7, 64), (1025, 4, 16), (1100, 4, 65), (2048, 3, 256),
-    (2049, 3, 9), (2500, 130, 130), (4097, 3, 32), (6145, 2, 256), (8192, 3, 40)])
+    (2049, 3, 9), (2500, 130, 130), (4097, 3, 32), (6145, 2, 256), (8192, 3, 40), (500, 1280, 97), (500, 1281, 97),
+    (500, 1025, 33), (300, 8193, 97), (513, 1537, 200), (768, 1025, 96), (769, 1025, 96), (769, 1025, 97),
+    (1025, 769, 96), (1280, 769, 1), (1281, 769, 40), (1536, 800, 96), (1536, 800, 97)])
 def test_topk_dispatch_edges(V, B, k):
     check_topk(V, B, k, asr_logprobs((B, V + 2), seed=V + k)[:, :V].copy())
 
 
-@pytest.mark.parametrize("V,k", [(100, 70), (300, 40), (512, 200), (1000, 1), (1000, 256), (1500, 100), (5000, 64)])
-def test_topk_ties_beyond_the_list(V, k):
+@pytest.mark.parametrize("V,k,B", [(100, 70, 6), (300, 40, 6), (512, 200, 6), (1000, 1, 6), (1000, 256, 6),
+                                   (1500, 100, 6), (5000, 64, 6), (700, 256, 1538), (1000, 90, 1026), (1200, 90, 770),
+                                   (1500, 90, 770)])
+def test_topk_ties_beyond_the_list(V, k, B):
     """lam = 0 and few distinct scores: hundreds of tokens share the k-th value, within
     and across wavefronts; rows with fewer than k scores above -inf; a row all at -inf."""
     rng = np.random.default_rng(V + k)
-    asr = rng.integers(-2, 1, (6, V)).astype(np.float32)
+    asr = rng.integers(-2, 1, (B, V)).astype(np.float32)
     asr[1] = 0.0
     asr[2] = -np.inf
     asr[3, rng.permutation(V)[:max(1, V - k // 2)]] = -np.inf
     asr[4] = np.where(np.arange(V) == V - 1, 1.0, -0.0)
     for lam in (0.0, 0.5):
-        check_topk(V, 6, k, asr, lam)
+        check_topk(V, B, k, asr, lam)
 
 
 @pytest.mark.parametrize("V,B,mode", [
