@@ -161,20 +161,31 @@ static hipError_t launch_group(const DevTrie &t, const float *asr, int64_t B, in
     return hipSuccess;
 }
 
-// Wavefronts and tokens per lane, from a sweep (CTC, us a step; the step before
-// this one held the row and the walk in LDS, four wavefronts up to 1024
-// hypotheses and one above, whatever the vocabulary):
+// Wavefronts and tokens per lane, from sweeps over vocabularies and 8 to 12000
+// hypotheses (CTC, us a step, without and from V = 513 on with the copies that
+// reset the state; "before": row and walk in LDS, four wavefronts up to 1024
+// hypotheses and one above, whatever the vocabulary).  Wavefronts pay off while
+// the chip has room; beyond, each one repeats the walk and the exchanges.
 //  - V <= 256: one of 4 a lane: 3.6 / 5.3 at V = 128, 8 / 4000 hypotheses [two of
 //    2: 3.9 / 6.9; before: 4.5 / 5.8].
 //  - V <= 512: one of 8: 3.7 / 5.9 at V = 400 [two of 4: 3.8 / 7.3; before: 4.4 / 6.8].
 //  - V <= 1024: four of 4 up to 768 hypotheses: 4.6 at 300 [two of 8: 5.0; before:
-//    5.4]; two of 8 above: 5.9 / 9.6 at 1500 / 4000 [6.1 / 10.8; before: 7.4 / 12.1].
+//    5.4]; two of 8 above: 5.9 / 9.6 at 1500 / 4000 [6.1 / 10.8; before: 7.4 / 12.1], up
+//    to V = 768 one of 12: 8.6 / 10.0 at V = 700, 2048 / 4096 [two of 8: 9.3 / 11.8;
+//    before: 8.7 / 10.5].
+//  - V <= 1536: eight of 4 up to 512 hypotheses (up to V = 1280 only 256: 8.1 at 400
+//    with two of 10 [8.8; before: 8.6]), two of 10 or 12 above: 9.7 / 13.5 at V = 1100,
+//    2048 / 4096 [four of 8: 11.5 / 17.1; before: 9.7 / 15.4].
 //  - V <= 2048: eight of 4 up to 512 hypotheses: 4.0 / 5.1 at 8 / 300 [four of 8:
 //    4.3 / 5.2; before: 5.0 / 5.8], four of 8 above: 15.5 at 4000 [17.9; before: 19.9].
+//  - V <= 3072: eight of 8 up to 512 hypotheses, four of 10 or 12 above: 10.1 / 21.3 at
+//    V = 2500, 900 / 4096 [eight of 8: 12.1 / 28.2; before: 11.0 / 29.0].
 //  - V <= 4096: eight of 8: 4.6 / 6.1 / 27.9 at V = 4000, 8 / 300 / 4000 [four of 16:
 //    5.2 / 6.7 / 28.0; before: 5.8 / 7.1 / 50].
-//  - above: sixteen of 8: 5.4 / 8.6 / 54 at V = 8000 [eight of 16: 5.7 / 8.8 / 55;
-//    before: 7.6 / 14.7 / 182].
+//  - above: sixteen of 8 for few hypotheses, 5.4 at V = 8000, 8 [eight of 16: 5.7;
+//    before: 7.6]; above 128 eight of 12 up to V = 6144, 10.8 / 15.9 / 38.5 at V = 5000,
+//    400 / 900 / 4096 [sixteen of 8: 12.8 / 18.3 / 54.9; before: 11.1 / 17.5 / 75], and
+//    eight of 16, 13.1 / 55.6 at V = 6200, 400 / 4096 [14.4 / 59.9; before: 13.8 / 92].
 template <int MODE>
 static hipError_t launch_mode(const DevTrie &t, const float *asr, int64_t B, int64_t ld, float lambda, int32_t *states,
                               int32_t *prev, int32_t *tokens, hipStream_t stream) {
@@ -184,14 +195,23 @@ static hipError_t launch_mode(const DevTrie &t, const float *asr, int64_t B, int
     if (V <= 512) NGPU_STEP(1, 8);
     if (V <= 1024) {
         if (B <= 768) NGPU_STEP(4, 4);
+        if (V <= 768) NGPU_STEP(1, 12);
         NGPU_STEP(2, 8);
     }
     if (V <= 2048) {
-        if (B <= 512) NGPU_STEP(8, 4);
+        if (B <= (V <= 1280 ? 256 : 512)) NGPU_STEP(8, 4);
+        if (V <= 1280) NGPU_STEP(2, 10);
+        if (V <= 1536) NGPU_STEP(2, 12);
         NGPU_STEP(4, 8);
     }
+    if (V <= 3072 && B > 512) {
+        if (V <= 2560) NGPU_STEP(4, 10);
+        NGPU_STEP(4, 12);
+    }
     if (V <= 4096) NGPU_STEP(8, 8);
-    NGPU_STEP(16, 8);
+    if (B <= 128) NGPU_STEP(16, 8);
+    if (V <= 6144) NGPU_STEP(8, 12);
+    NGPU_STEP(8, 16);
 #undef NGPU_STEP
 }
 

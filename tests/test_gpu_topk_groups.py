@@ -69,7 +69,10 @@ def test_topk_ties_beyond_the_list(V, k, B):
     (1, 3, MODE_CTC), (63, 3, MODE_TRANSDUCER), (256, 5, MODE_AED), (257, 5, MODE_CTC), (512, 5, MODE_PLAIN),
     (513, 768, MODE_CTC), (700, 769, MODE_AED), (1024, 900, MODE_TRANSDUCER), (1025, 512, MODE_CTC),
     (1100, 9, MODE_AED), (2048, 513, MODE_PLAIN), (2049, 9, MODE_CTC), (4096, 5, MODE_AED), (4500, 9, MODE_CTC),
-    (8192, 3, MODE_TRANSDUCER)])
+    (8192, 3, MODE_TRANSDUCER), (513, 769, MODE_CTC), (768, 769, MODE_AED), (769, 769, MODE_CTC),
+    (1025, 257, MODE_TRANSDUCER), (1280, 257, MODE_CTC), (1281, 513, MODE_AED), (1536, 513, MODE_CTC),
+    (2049, 513, MODE_CTC), (2560, 513, MODE_AED), (2561, 513, MODE_PLAIN), (3072, 513, MODE_CTC),
+    (4097, 129, MODE_CTC), (6144, 129, MODE_AED), (6145, 129, MODE_TRANSDUCER), (8192, 129, MODE_CTC)])
 def test_step_dispatch_edges(V, B, mode):
     m, lm, o = model(V, mode == MODE_AED)
     states = uniform_states(m, B, seed=V + 1)
