@@ -263,7 +263,8 @@ __device__ __forceinline__ int pick(const Words<NT> &x, int j, int l) {
     }
 }
 
-// One wavefront per utterance, 16 tokens a lane: large batches, where the
+// One wavefront per utterance, 16 tokens a lane (20 and 32 for the batches in
+// launch_mode): large batches, where the
 // launch is bound by the ASR rows' stream and by instruction issue rather than
 // by one utterance's chain.  COMPACT: the 4-byte dense rows, half the traffic;
 // the winner's next state then follows from the row's rules (DevTrie).  The
@@ -516,18 +517,23 @@ static hipError_t launch_group(const Decode &d) {
     return full ? launch_group<MODE, W, NT, true, kKeep>(d) : launch_group<MODE, W, NT, false, kKeep>(d);
 }
 
-template <int MODE, bool FULL, bool COMPACT>
+template <int MODE, int NT, bool FULL, bool COMPACT>
 static hipError_t launch_wave(const Decode &d) {
-    constexpr int NT = 16;
     hipLaunchKernelGGL((decode_wave_kernel<MODE, NT, FULL, COMPACT>), dim3(unsigned(d.B)), dim3(kWave),
                        size_t(kWave) * NT * sizeof(i32x2), d.stream, d.t, d.uni_base, d.asr, d.T, d.st, d.sb, d.lengths,
                        d.lambda, d.states, d.prev, d.labels, d.label_states);
     return hipGetLastError();
 }
 
-template <int MODE, bool FULL>
+template <int MODE, int NT, bool FULL>
 static hipError_t launch_wave(const Decode &d) {
-    return d.t.dense_c ? launch_wave<MODE, FULL, true>(d) : launch_wave<MODE, FULL, false>(d);
+    if constexpr (NT * kWave <= 1024)   // larger vocabularies have no compact rows
+        if (d.t.dense_c) return launch_wave<MODE, NT, FULL, true>(d);
+    return launch_wave<MODE, NT, FULL, false>(d);
+}
+template <int MODE, int NT>
+static hipError_t launch_wave(const Decode &d) {
+    return d.t.vocab_size == NT * kWave ? launch_wave<MODE, NT, true>(d) : launch_wave<MODE, NT, false>(d);
 }
 
 // Wavefronts and tokens per lane, from a sweep over vocabularies and batches
@@ -539,9 +545,22 @@ static hipError_t launch_wave(const Decode &d) {
 //    204 against 277 at 512, 249 against 275 at 1024, 410 against 289 at 1500,
 //    836 against 427 at 4096.  Two wavefronts (8 a lane) win only near 1500,
 //    by 2 %.
+//  - V <= 1280 (50 frames; "before": one wavefront per utterance above 512, rows
+//    in LDS): eight wavefronts up to 768 utterances, two of 10 a lane up to 2048: 106
+//    / 141 at V = 1100, 1024 / 1500 [four of 8: 129 / 211; before: 164 / 185]; one of 20
+//    above: 176 / 189 at 2500 / 4096 [two of 10: 219 / 195; before: 336 / 248].
+//  - V <= 1536: four of 6 above 768: 121 / 210 / 216 at V = 1300, 1024 / 2500 / 4096
+//    [four of 8: 135 / 263 / 250; before: 194 / 332 / 249], but two of 12 at 1153 to
+//    1536, which are all resident then (six a CU): 153 at 1500 [four of 6: 201; before:
+//    210].
 //  - V <= 2048: eight wavefronts while every utterance of the batch is resident
-//    (156 against 181 for four at 64, 206 against 207 at 500), four above (467
-//    against 515 at 1200, 636 against 766 at 2500).
+//    (156 against 181 for four at 64, 206 against 207 at 500, 100 frames), four above
+//    (467 against 515 at 1200, 636 against 766 at 2500).  Four leave a nearly empty
+//    second round at 1280 to 1536: one of 32 there, 204 / 152 at V = 2000, 1500
+//    (CTC / transducer) [four: 218 / 153; before: 235 / 178].
+//  - V <= 2560: eight of 8 up to 512 utterances, four of 10 above: 145 / 218 / 211 at
+//    V = 2500, 700 / 1500 / 4096 (50 / 35 / 13 frames) [eight: 221 / 274 / 283; before:
+//    264 / 384 / 282].
 //  - V <= 4096: eight wavefronts of 8 a lane: 193 / 325 / 670 at 64 / 500 / 1200
 //    (four of 16: 260 / 332 / 725; sixteen of 4: 189 / 402 / 831).
 //  - above: sixteen of 8 a lane: 290 / 671 / 720 at 64 / 500 / 1200 (42 frames)
@@ -552,10 +571,16 @@ static hipError_t launch_mode(const Decode &d) {
     if (V <= 256) return launch_group<MODE, 1, 4>(d);
     if (V <= 512) return launch_group<MODE, 1, 8>(d);
     if (V <= 1024) {
-        if (d.B <= 1024) return launch_group<MODE, 4, 4>(d);
-        return V == 1024 ? launch_wave<MODE, true>(d) : launch_wave<MODE, false>(d);
+        return d.B <= 1024 ? launch_group<MODE, 4, 4>(d) : launch_wave<MODE, 16>(d);
     }
-    if (V <= 2048) return d.B <= 768 ? launch_group<MODE, 8, 4>(d) : launch_group<MODE, 4, 8>(d);
+    if (V <= 2048) {
+        if (d.B <= 768) return launch_group<MODE, 8, 4>(d);
+        if (V <= 1280) return d.B <= 2048 ? launch_group<MODE, 2, 10>(d) : launch_wave<MODE, 20>(d);
+        if (V <= 1536) return d.B > 1152 && d.B <= 1536 ? launch_group<MODE, 2, 12>(d) : launch_group<MODE, 4, 6>(d);
+        if (d.B > 1280 && d.B <= 1536) return launch_wave<MODE, 32>(d);
+        return launch_group<MODE, 4, 8>(d);
+    }
+    if (V <= 2560 && d.B > 512) return launch_group<MODE, 4, 10>(d);
     if (V <= 4096) return launch_group<MODE, 8, 8>(d);
     return launch_group<MODE, 16, 8>(d);
 }

@@ -39,7 +39,11 @@ def check(m, asr, mode, starts, prev=None, lengths=None, lam=0.5):
     (255, 9, MODE_CTC), (256, 3, MODE_AED), (257, 9, MODE_TRANSDUCER), (512, 70, MODE_CTC), (513, 1024, MODE_PLAIN),
     (768, 17, MODE_AED), (900, 1025, MODE_TRANSDUCER), (1024, 1024, MODE_CTC), (1024, 1025, MODE_AED),
     (1025, 768, MODE_CTC), (2047, 769, MODE_TRANSDUCER), (2049, 33, MODE_AED), (4096, 5, MODE_CTC),
-    (4097, 6, MODE_PLAIN), (8192, 3, MODE_CTC)])
+    (4097, 6, MODE_PLAIN), (8192, 3, MODE_CTC), (1025, 769, MODE_CTC), (1280, 2048, MODE_AED),
+    (1025, 2049, MODE_TRANSDUCER), (1100, 2049, MODE_CTC), (1280, 2049, MODE_PLAIN), (1281, 769, MODE_CTC),
+    (1281, 1153, MODE_TRANSDUCER), (1536, 1536, MODE_PLAIN), (1536, 1537, MODE_CTC), (1281, 1537, MODE_AED),
+    (1537, 1280, MODE_CTC), (1537, 1281, MODE_CTC), (2047, 1400, MODE_AED), (2048, 1536, MODE_TRANSDUCER),
+    (2049, 513, MODE_CTC), (2560, 513, MODE_AED), (2561, 513, MODE_PLAIN)])
 def test_decode_dispatch_edges(V, B, mode):
     m = generate_model(V, [V, 4 * V, 3 * V, V], 1.0, seed=V, bos_eos=mode == MODE_AED)
     T = 130 if B < 100 else 9   # past the 64 frames whose labels are stored at once, and not a multiple of it
@@ -49,7 +53,8 @@ def test_decode_dispatch_edges(V, B, mode):
     check(m, asr, mode, uniform_states(m, B, seed=V + B), lengths=lengths)
 
 
-@pytest.mark.parametrize("V,B", [(300, 8), (700, 8), (700, 1100), (1500, 8)])
+@pytest.mark.parametrize("V,B", [(300, 8), (700, 8), (700, 1100), (1100, 800), (1100, 2050), (1500, 8), (1500, 1200),
+                                 (1500, 1540), (1600, 1300), (2100, 520)])
 def test_decode_ties_and_empty_candidate_sets(V, B):
     """Rows of few distinct scores (ties within a lane, across lanes and across
     wavefronts go to the lowest token), rows all at -inf, and previous labels at

@@ -64,7 +64,8 @@ def without_nan(asr):
     (700, 64, MODE_CTC, True), (700, 1100, MODE_PLAIN, True), (700, 1100, MODE_CTC, True), (700, 1100, MODE_AED, True),
     (700, 1100, MODE_PLAIN, False), (700, 1100, MODE_TRANSDUCER, False), (1024, 1100, MODE_CTC, True),
     (1024, 1100, MODE_PLAIN, True), (1024, 64, MODE_TRANSDUCER, True), (1500, 64, MODE_CTC, True),
-    (1500, 800, MODE_PLAIN, True), (4096, 33, MODE_AED, True), (4097, 33, MODE_PLAIN, True),
+    (1500, 800, MODE_PLAIN, True), (1100, 2049, MODE_PLAIN, True), (1100, 2049, MODE_CTC, True),
+    (1900, 1281, MODE_AED, True), (4096, 33, MODE_AED, True), (4097, 33, MODE_PLAIN, True),
     (4097, 33, MODE_CTC, True)])
 def test_greedy(V, B, mode, dense4):
     if not torch.cuda.is_available():
