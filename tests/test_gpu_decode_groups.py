@@ -80,13 +80,28 @@ def test_decode_without_every_unigram(V, N, n1):
     check(m, asr, MODE_CTC, uniform_states(m, 12, seed=6))
 
 
-@pytest.mark.parametrize("V,B,T,mode", [(900, 1030, 75, MODE_TRANSDUCER), (2000, 700, 50, MODE_CTC)])
-def test_decode_streamed_rows(V, B, T, mode):
-    """ASR tensors above 256 MiB, whose rows are loaded non-temporally (the other
-    widths are decoded that way by the 20M 6-gram's tests)."""
+_NOISE = []
+
+
+@pytest.mark.parametrize("V,B,mode", [
+    (900, 1000, MODE_TRANSDUCER), (1100, 700, MODE_CTC), (2048, 700, MODE_TRANSDUCER), (1100, 1000, MODE_CTC),
+    (1280, 1000, MODE_TRANSDUCER), (1400, 1300, MODE_CTC), (1536, 1300, MODE_CTC), (1400, 1000, MODE_TRANSDUCER),
+    (1536, 1000, MODE_CTC), (2000, 800, MODE_CTC), (2048, 800, MODE_CTC), (2300, 600, MODE_TRANSDUCER),
+    (2560, 600, MODE_CTC), (3000, 500, MODE_CTC), (4096, 500, MODE_TRANSDUCER), (5000, 300, MODE_CTC),
+    (8192, 200, MODE_TRANSDUCER)])
+def test_decode_streamed_rows(V, B, mode):
+    """ASR tensors just above 256 MiB, whose rows are loaded non-temporally by every
+    kernel of several wavefronts per utterance: each width the launcher has for
+    them, with lanes past V and without (V = 1024 with four wavefronts is decoded
+    that way by the 20M 6-gram's test).  About two frames in three are blank."""
     m = generate_model(V, [V, 4 * V, 3 * V], 1.0, seed=V)
-    g = np.random.default_rng(V)
-    asr = g.standard_normal((B, T, V + 1), dtype=np.float32) * 3.0
-    asr[:, :, V] += 4.0
+    T = (1 << 26) // (B * (V + 1)) + 1
+    n = B * T * (V + 1)
+    if not _NOISE:
+        _NOISE.append(np.random.default_rng(0).standard_normal((1 << 26) + (1 << 22), dtype=np.float32) * 3.0)
+    asr = _NOISE[0][:n].reshape(B, T, V + 1).copy()
+    asr[:, :, V] += 3.0 * np.sqrt(2.0 * np.log(V))   # near the largest of V such scores
     assert asr.nbytes > 256 << 20
-    check(m, asr, mode, uniform_states(m, B, seed=9))
+    labels = check(m, asr, mode, uniform_states(m, B, seed=9))
+    spoken = (labels.cpu().numpy() != V).mean()
+    assert 0.1 < spoken < 0.9
