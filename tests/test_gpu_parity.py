@@ -469,14 +469,12 @@ def test_fused_larger_batches(dev, B):
 @pytest.mark.parametrize("V,B", [(40, 10000), (1000, 2400), (1024, 2400), (1025, 600), (1025, 2000), (2048, 1000),
                                  (2048, 1500)])
 def test_decode_launch_row_placements(dev, V, B):
-    """The whole decode with one wavefront per utterance keeps the ASR rows in
-    registers up to V = 1024 when the model has 4-byte dense rows (these
-    models do; with and without a last register chunk cut short by V, or with
-    most chunks past V); above V = 1024 in two LDS buffers while every
-    utterance is resident at once with them (on 256 CUs with 160 KiB of LDS
-    each: 1792 at V = 1025, 1024 at V = 2048), else in one LDS buffer.  The
-    cases cover each placement, and the four fusion modes on the register
-    paths."""
+    """The whole decode of large batches at both sides of V = 1024 and at tile edges:
+    one wavefront per utterance with 4 tokens a lane (V = 40) and with 16 and
+    4-byte dense rows (V = 1000 and 1024, with lanes past V and without), and
+    several wavefronts with a last tile of one token (V = 1025) and with every
+    lane in use (V = 2048), which may put a tie's tokens in different
+    wavefronts.  Ragged lengths; the four fusion modes up to V = 1024."""
     m, lm, o = pair(f"V{V}", lambda: generate_model(V, [V, 20000, 15000], 1.0, seed=V, bos_eos=True))
     T = 10
     starts = uniform_states(m, B, seed=B + 3)
