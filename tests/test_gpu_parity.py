@@ -157,12 +157,12 @@ def test_advance_6gram_20m_bench_launch_sampled(dev):
 
 @pytest.mark.parametrize("which", ["4gram_200k", "V800", "V1025", "N10"])
 def test_advance_grouped_mapping_with_bad_states(dev, which):
-    """Batches of 20480 and more take the XCD-grouped mapping: every row, including
-    rows of out-of-range states (written by exactly one owner), vs the oracle.
-    V in (768, 1024] runs it with two wavefronts per hypothesis, one per
-    512-token half (V = 800: a ragged second half); V = 1025 with one.
-    N10: a 10-gram, whose order-9 states have chain records longer than the
-    scan preloads."""
+    """Batches of 20480 and more: every row, including rows of out-of-range states
+    (written by exactly one owner), vs the oracle.  V = 1024 takes the XCD-grouped
+    mapping with two wavefronts per hypothesis; V = 800 two wavefronts in a
+    workgroup, the second with a short range; V = 1025 four, without 16-byte
+    stores; N10, a 10-gram of 16 tokens, one wavefront with chain records of nine
+    levels."""
     if which == "4gram_200k":
         m, lm, o = model_pair("fourgram_200k")
         B = 40000
@@ -204,10 +204,10 @@ def test_advance_odd_shapes(dev, V, N):
 
 @pytest.mark.parametrize("V,N", [(5, 3), (300, 3), (700, 3), (1025, 4), (4096, 3), (16, 10)])
 def test_advance_small_batches_every_stripe_count(dev, V, N):
-    """Batches of up to 1024 hypotheses run with one wavefront per 256-token
-    stripe, at most four: V = 5 and 16 one stripe, 300 two, 700 three stripes
-    on two wavefronts, 1025 (no 16-byte stores) and 4096 four.  Out-of-range
-    states among them give rows of NaN / -1 and are counted."""
+    """A batch of 700 on one wavefront per hypothesis (V = 5 and 16), two (300), three
+    (700; 1025 without 16-byte stores) and eight (4096), the last of which may
+    hold few tokens.  Out-of-range states among them give rows of NaN / -1 and
+    are counted."""
     if N == 10:
         counts = [V, 120, 200, 200, 180, 160, 140, 120, 100, 80]
     else:
@@ -447,10 +447,9 @@ def test_decode_launch_modes_ragged_lengths(dev, mode):
 
 @pytest.mark.parametrize("B", [513, 1100, 5000])
 def test_fused_larger_batches(dev, B):
-    """Batches above 512 hypotheses: the whole decode runs with one wavefront
-    per hypothesis instead of four (the per-frame step from 1025 on, so 513
-    covers its four-wavefront path at that size), with the ASR rows and the
-    4-byte dense rows in registers (this model has them)."""
+    """V = 1024: the whole decode with four wavefronts per utterance (513) and with
+    one and 4-byte dense rows (1100 and 5000), the per-frame step with four (513)
+    and two."""
     m, lm, o = model_pair("fourgram_200k")
     V = m.vocab_size
     T = 16
@@ -530,9 +529,9 @@ def test_decode_register_rows_dense_forms(dev, which):
 def test_decode_launch_time_major_view(dev, V, B):
     """The whole decode reads a time-major [T, B, C] buffer through a permuted
     [B, T, C] view (utterance stride C, frame stride B * C) whose rows carry
-    padding past the classes: four wavefronts with LDS rows, and registers
-    with and without a short last chunk, must read only the V (+ 1) classes
-    of its own row."""
+    padding past the classes: four wavefronts per utterance (32, 600) and one,
+    with and without lanes past V, must read only the V (+ 1) classes of its
+    own row."""
     if V == 1024:
         m, lm, o = model_pair("fourgram_200k")
     else:
@@ -560,9 +559,9 @@ def test_decode_launch_time_major_view(dev, V, B):
 
 @pytest.mark.parametrize("B", [200, 2400])
 def test_decode_launch_lambda_signs(dev, B):
-    """Negative, zero and large lambda on the four-wavefront LDS path (200
-    utterances) and the one-wavefront register path (2400): the CTC exclusion
-    of the previous label must hold whatever sign the LM term takes."""
+    """Negative, zero and large lambda with four wavefronts per utterance (200)
+    and with one (2400): the CTC exclusion of the previous label must hold
+    whatever sign the LM term takes."""
     m, lm, o = model_pair("fourgram_200k")
     V = m.vocab_size
     T = 12
@@ -643,8 +642,8 @@ def test_fused_ties_lambda_zero_and_all_blank(dev):
 
 
 def _edge_frames(V, B):
-    """Frames whose argmax hinges on -inf and on ties across lanes and stripes
-    (tokens go four to a lane in stripes of 256)."""
+    """Frames whose argmax hinges on -inf and on ties between tokens of one lane, of
+    two lanes and of two wavefronts (lanes hold every 64th token)."""
     ninf = -np.inf
     asr = asr_logprobs((B, 8, V + 1), seed=13, blank_boost=0.5)
     asr[:, 0, :] = ninf                                    # every class at -inf
@@ -698,8 +697,8 @@ def test_aed_minus_inf_frames(dev):
 
 
 def test_max_vocabulary(dev):
-    """V = 8192, the largest vocabulary the library takes: the LDS rows of
-    every kernel at their largest."""
+    """V = 8192, the largest vocabulary the library takes: the groups of every
+    kernel at their widest, with 64 KiB of slots."""
     m, lm, o = pair("V8192", lambda: generate_model(8192, [8192, 40000, 30000], 1.0, seed=8192))
     V = m.vocab_size
     assert V == 8192
@@ -715,7 +714,7 @@ def test_max_vocabulary(dev):
         gl, gs, _, _ = gpu_decode_launch(lm, a, mode, 0.5, starts, dev)
         ol, os_ = o.decode(a, mode, 0.5, starts, nthreads=NTHREADS)
         assert np.array_equal(gl, ol) and np.array_equal(gs, os_)
-    # above 512 utterances: one wavefront each, one LDS row buffer (98 KiB of LDS per workgroup)
+    # more utterances than the chip holds at once (sixteen wavefronts each)
     B2, T2 = 600, 6
     starts2 = uniform_states(m, B2, seed=18)
     asr2 = asr_logprobs((B2, T2, V + 1), seed=19, blank_boost=1.0)
@@ -805,8 +804,8 @@ def test_fused_topk_minus_inf_and_ties(dev, lam):
 
 @pytest.mark.parametrize("V", [128, 500, 700])
 def test_fused_topk_vocab_sizes(dev, V):
-    """Vocabularies of one, two and three 256-token stripes per lane (the
-    register top-k), with -inf rows and ties."""
+    """One wavefront of 4 and of 8 tokens a lane, and four wavefronts the last of
+    which holds no token, with -inf rows and ties."""
     m, lm, o = pair(f"topk V{V}", lambda: generate_model(V, [V, 6 * V, 6 * V], 1.0, seed=V + 7))
     B, k = 40, 12
     states = uniform_states(m, B, seed=V + 8)
@@ -846,12 +845,11 @@ def test_sync_check(dev):
 
 @pytest.mark.parametrize("k", [6, 8, 64, 100, 128, 256])
 def test_fused_topk_large_k(dev, k):
-    """The threshold selection (every k at V <= 1024) at larger k: rows of full
-    ties, -inf rows, rows with fewer finite tokens than k, rows whose fused
-    values are coarsely quantised so that many tokens tie across lanes and
-    stripes, and ordinary rows.  k = 64 and 128 are the largest k whose search
-    starts from the smallest lane maximum and lane second-maximum; above 128 it
-    starts from no lower bound."""
+    """Top-k at larger k: rows of full ties, -inf rows, rows with fewer finite
+    tokens than k, rows whose fused values are coarsely quantised so that many
+    tokens tie across lanes and wavefronts, and ordinary rows.  With four
+    wavefronts of 64 lanes the lower bound comes from the maxima of rows of 16
+    lanes (k = 6 to 16), of groups of 4 lanes (64) and of single lanes (above)."""
     m, lm, o = model_pair("fourgram_200k")
     V = m.vocab_size
     B = 24
