@@ -271,9 +271,9 @@ __device__ __forceinline__ int pick(const Words<NT> &x, int j, int l) {
 // plain argmax needs the row's maximum only (three-input maxima): blank is
 // above it or not, and a repeat is the previous label holding it; the winner's
 // token is searched where the wave's maximum is found.  4096 utterances x 200
-// frames, V = 1024: 811 us (820 in the kernel before, 8-byte slots and one frame's
-// chain in line), 883 (893) on rows just written; without any LM work the stream
-// of ASR rows (3.36 GB) alone takes 670.  V = 700, 100 frames: 329 us (673 before).
+// frames, V = 1024: 813 us (822 in the kernel before, 8-byte slots and one frame's
+// chain in line), 843 (847) on rows just written; without any LM work the stream
+// of ASR rows (3.36 GB) alone takes 670.  V = 700, 100 frames: 326 us (654 before).
 template <int MODE, int NT, bool FULL, bool COMPACT>
 __global__ __launch_bounds__(kWave, (COMPACT ? 4 : 1)) void decode_wave_kernel(
     DevTrie t, int uni_base, const float *__restrict__ asr, int64_t T, int64_t stride_t, int64_t stride_b,
@@ -504,8 +504,8 @@ static hipError_t launch_group(const Decode &d) {
 
 // Rows of up to 512 tokens are always kept: streamed, V = 128 took 143 against
 // 136 us at 1500 utterances, 178 against 165 at 4000 (two rows share a line).  So
-// are those of decode_wave_kernel: streamed, 4096 x 200 took 800 instead of 820 us
-// repeated, but 903 instead of 883 on a tensor just written, which a decode
+// are those of decode_wave_kernel: streamed, 4096 x 200 took 795 instead of 813 us
+// repeated, but 888 instead of 843 on a tensor just written, which a decode
 // after the acoustic model finds.
 template <int MODE, int W, int NT>
 static hipError_t launch_group(const Decode &d) {

@@ -46,8 +46,9 @@ constexpr int kBufferConfig = 0x00020000;
 // once, with one wait; later reads reuse the values (kernel arguments are
 // constant) or hit the scalar cache.  The asm statements count as memory
 // accesses, so uniform loads from global memory after them are vector loads.
-// Used by the small-batch kernels only: kernels with a loop over hypotheses or
-// frames would hold the values in scalar registers throughout and spill.
+// Used by the kernels that serve one hypothesis a group and end (query, step,
+// top-k), at every batch size: kernels with a loop over hypotheses or frames
+// would hold the values in scalar registers throughout and spill.
 template <class T>
 __device__ __forceinline__ void load_arg(const T &v) {
     asm volatile("" ::"s"(v));
