@@ -77,6 +77,11 @@ __global__ __launch_bounds__(W * kWave) void decode_kernel(DevTrie t, int uni_ba
     const float *row = asr + b * stride_b;
     unsigned raw_key = 0;   // the frame's best class by its ASR scores alone: key and token
     int raw_tok = 0, xi = 0;
+    // key of blank's score, NaN as -inf, taken off the chain while the frame before it runs
+    auto blank_key_of = [](float v) {
+        return unsigned(__builtin_amdgcn_readfirstlane(int(float_key(or_lowest(v)))));
+    };
+    unsigned blank_key = 0;
     if (len > 0) {
         load_row(row, cur, cur_v);
         fetch_rec(s);
@@ -86,6 +91,7 @@ __global__ __launch_bounds__(W * kWave) void decode_kernel(DevTrie t, int uni_ba
         g.mask_row(cur);
         if (kRaw) {
             g.raw_best(cur, raw_key, raw_tok);
+            blank_key = blank_key_of(cur_v);
             if (W > 1) {
                 if (lane == 0) {
                     meet->a[0][wave].w = raw_tok;
@@ -110,16 +116,17 @@ __global__ __launch_bounds__(W * kWave) void decode_kernel(DevTrie t, int uni_ba
             row += f + 2 < left ? stride_t : 0;   // row f + 2 (at the end the last row again, not used)
             load_row(row, nn, nn_v);
             g.mask_row(nxt);
-            unsigned nr_key = 0;
+            unsigned nr_key = 0, nr_blank = 0;
             int nr_tok = 0;
-            if (kRaw) g.raw_best(nxt, nr_key, nr_tok);
-            const float rowV = MODE == kPlain ? 0.0f
-                                              : __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(cur_v)));
+            if (kRaw) {
+                g.raw_best(nxt, nr_key, nr_tok);
+                nr_blank = blank_key_of(nxt_v);
+            }
             int label = -1;
             bool lm = true;
             if (kRaw) {
                 label = raw_tok;                                      // every token at -inf: the lowest, 0
-                if (float_key(or_lowest(rowV)) > raw_key) label = V;  // blank only when strictly larger (highest index)
+                if (blank_key > raw_key) label = V;                   // blank only when strictly larger (highest index)
                 lm = !(label == V || (MODE == kCtc && label == pv));  // blank or repeat: no LM, no move
             }
             unsigned fkey = 0;
@@ -177,6 +184,7 @@ __global__ __launch_bounds__(W * kWave) void decode_kernel(DevTrie t, int uni_ba
             bool moved = lm;
             if (MODE == kAed) {   // <eos> strictly above every token: the sentence ends, the state stays
                 const float fw = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(fin)));
+                const float rowV = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(cur_v)));
                 if (float_key(or_lowest(__builtin_fmaf(lambda, fw, rowV))) > fkey) {
                     label = V;
                     moved = false;
@@ -210,6 +218,7 @@ __global__ __launch_bounds__(W * kWave) void decode_kernel(DevTrie t, int uni_ba
             }
             raw_key = nr_key;
             raw_tok = nr_tok;
+            blank_key = nr_blank;
             cur = nxt;
             cur_v = nxt_v;
             nxt = nn;
